@@ -831,16 +831,21 @@ int path_for(hfd_plan p, int batch)
     return it != p->tuned.end() ? it->second.path : p->path;
 }
 
-// rows per block of the x passes: the tuned choice, else the largest compiled
-// tile that still gives every CU at least one block
+// Rows per block of the x passes: the tuned choice, else the largest compiled
+// tile that leaves more than 192 blocks (3/4 of the CUs), at least the default
+// one of 16 (FP64 8) rows.  Taller tiles write longer runs of y per kx: the
+// forward pass of 16 states of 256 x 256 x 10 takes 147 / 118 / 106 / 94 us at
+// 8 / 16 / 24 / 32 rows.  Fewer blocks than that leave CUs idle: 128 x 128 x 8
+// (3072 rows) runs at 21.0 / 19.9 / 21.2 / 21.6 us per field, 256 x 256 x 8 (6144)
+// at 39.1 / 36.0 / 35.2 / 36.0.
 int xty_for(hfd_plan p, int batch)
 {
     auto it = p->tuned.find(batch);
     if (it != p->tuned.end()) return it->second.xty;
     const long long rows = (long long)batch * 3 * p->nz * p->ny;
     int best = 0;
-    for (int ty : {8, 16, 24, 32})
-        if (x_tile_supported(p->fp64, p->Lx, ty) && (rows + ty - 1) / ty >= 256) best = ty;
+    for (int ty : {16, 24, 32})
+        if (x_tile_supported(p->fp64, p->Lx, ty) && (rows + ty - 1) / ty > 192) best = ty;
     return best;
 }
 
@@ -906,13 +911,11 @@ hfd_status run_field(hfd_plan p, const void* in, void* out, int batch, int adjoi
             char* out_c = (char*)out + (size_t)b0 * state;
             const int* qs_c = p->qslot + (size_t)g0 * p->P;
             const char* lp_c = (const char*)p->lp + (size_t)g0 * 2 * p->nz * p->rsz;
-            HFD_HIP(launch_xfwd(p->fp64, p->Lx, in_c, x1, p->nx, p->ny, (long long)p->ny * p->nx,
-                                p->nx, chunk * S, p->twx, s, xty));
+            HFD_HIP(launch_xfwd(p->fp64, p->Lx, in_c, x1, p->nx, p->ny, chunk * S, p->twx, s, xty));
             HFD_HIP(launch_fused(p->fp64, p->Ly, p->nz, x1, p->ny, p->M, chunk, p->Q, p->qcs, qs_c,
                                  p->QX, p->QY, lp_c, bpg_c, adjoint, p->twy, s,
                                  gen));
-            HFD_HIP(launch_xinv(p->fp64, p->Lx, x1, out_c, p->nx, p->ny, (long long)p->ny * p->nx,
-                                p->nx, chunk * S, p->twx, s, xty));
+            HFD_HIP(launch_xinv(p->fp64, p->Lx, x1, out_c, p->nx, p->ny, chunk * S, p->twx, s, xty));
         }
         if (nstage) *nstage = 3;
         return HFD_OK;
@@ -925,8 +928,7 @@ hfd_status run_field(hfd_plan p, const void* in, void* out, int batch, int adjoi
     };
     auto on = [&]() { return only < 0 || only == k; };
     if (on())
-        HFD_HIP(launch_xfwd(p->fp64, p->Lx, in, x1, p->nx, p->ny, (long long)p->ny * p->nx, p->nx,
-                            nsig, p->twx, s, xty));
+        HFD_HIP(launch_xfwd(p->fp64, p->Lx, in, x1, p->nx, p->ny, nsig, p->twx, s, xty));
     mark();
     if (path == 0) {
         if (on())
@@ -963,8 +965,7 @@ hfd_status run_field(hfd_plan p, const void* in, void* out, int batch, int adjoi
         mark();
     }
     if (on())
-        HFD_HIP(launch_xinv(p->fp64, p->Lx, x1, out, p->nx, p->ny, (long long)p->ny * p->nx, p->nx,
-                            nsig, p->twx, s, xty));
+        HFD_HIP(launch_xinv(p->fp64, p->Lx, x1, out, p->nx, p->ny, nsig, p->twx, s, xty));
     mark();
     if (nstage) *nstage = k;
     return HFD_OK;
@@ -1193,21 +1194,18 @@ static hfd_status adjoint_and_spectra(hfd_plan p, const void* gh, void* gm, int 
     const int xty = xty_for(p, batch);
     const size_t state = (size_t)S * p->ny * p->nx * p->rsz;
     const size_t hstate = (size_t)S * p->M * p->Ly * p->csz;
-    const long long sig_stride = (long long)p->ny * p->nx;
     for (int b0 = 0; b0 < batch; b0 += chunk) {
         const int g0 = b0 / bpg;
         const int bpg_c = bpg >= chunk ? chunk : bpg;
         const char* in_c = (const char*)gh + (size_t)b0 * state;
         char* out_c = (char*)gm + (size_t)b0 * state;
         const char* lp_c = (const char*)p->lp + (size_t)g0 * 2 * p->nz * p->rsz;
-        HFD_HIP(launch_xfwd(p->fp64, p->Lx, in_c, p->X1, p->nx, p->ny, sig_stride, p->nx, chunk * S,
-                            p->twx, s, xty));
+        HFD_HIP(launch_xfwd(p->fp64, p->Lx, in_c, p->X1, p->nx, p->ny, chunk * S, p->twx, s, xty));
         HFD_HIP(launch_yfwd(p->fp64, p->Ly, p->X1, (char*)p->Hh + (size_t)b0 * hstate, p->ny,
                             (long long)chunk * S * p->M, p->twy, s));
         HFD_HIP(launch_fused(p->fp64, p->Ly, p->nz, p->X1, p->ny, p->M, chunk, p->Q, p->qcs,
                              p->qslot + (size_t)g0 * p->P, p->QX, p->QY, lp_c, bpg_c, 1, p->twy, s, gen));
-        HFD_HIP(launch_xinv(p->fp64, p->Lx, p->X1, out_c, p->nx, p->ny, sig_stride, p->nx, chunk * S,
-                            p->twx, s, xty));
+        HFD_HIP(launch_xinv(p->fp64, p->Lx, p->X1, out_c, p->nx, p->ny, chunk * S, p->twx, s, xty));
     }
     return HFD_OK;
 }
@@ -1235,16 +1233,15 @@ hfd_status hfd_demag_vjp(hfd_plan p, const void* m, const void* grad_h, void* gr
     if (!grad_thickness) return run_field(p, grad_h, grad_m, batch, 1, s);
     const int nsig = batch * 3 * p->nz;
     const long long ncols = (long long)nsig * p->M;
-    const long long sig_stride = (long long)p->ny * p->nx;
     if (grad_m && path_for(p, batch) == 0) {
         HFD_TRY(adjoint_and_spectra(p, grad_h, grad_m, batch, s));
     } else {
         // (the five-pass paths use Mh and Hh themselves: grad_m first)
         if (grad_m) HFD_TRY(run_field(p, grad_h, grad_m, batch, 1, s));
-        HFD_HIP(launch_xfwd(p->fp64, p->Lx, grad_h, p->X1, p->nx, p->ny, sig_stride, p->nx, nsig, p->twx, s));
+        HFD_HIP(launch_xfwd(p->fp64, p->Lx, grad_h, p->X1, p->nx, p->ny, nsig, p->twx, s));
         HFD_HIP(launch_yfwd(p->fp64, p->Ly, p->X1, p->Hh, p->ny, ncols, p->twy, s));
     }
-    HFD_HIP(launch_xfwd(p->fp64, p->Lx, m, p->X1, p->nx, p->ny, sig_stride, p->nx, nsig, p->twx, s));
+    HFD_HIP(launch_xfwd(p->fp64, p->Lx, m, p->X1, p->nx, p->ny, nsig, p->twx, s));
     HFD_HIP(launch_yfwd(p->fp64, p->Ly, p->X1, p->Mh, p->ny, ncols, p->twy, s));
     const int bpg = batch / p->G;
     const bool stored = (p->flags & HFD_STORE_DTENSOR) != 0;
@@ -1568,7 +1565,7 @@ hfd_status hfd_forward_spectrum(hfd_plan p, const void* m, void* dst, long long 
     HFD_HIP(dg.set(p->dev));
     hipStream_t s = (hipStream_t)stream;
     const int nsig = batch * 3 * p->nz;
-    HFD_HIP(launch_xfwd(p->fp64, p->Lx, m, p->X1, p->nx, p->ny, (long long)p->ny * p->nx, p->nx, nsig, p->twx, s));
+    HFD_HIP(launch_xfwd(p->fp64, p->Lx, m, p->X1, p->nx, p->ny, nsig, p->twx, s));
     HFD_HIP(launch_yfwd(p->fp64, p->Ly, p->X1, dst, p->ny, (long long)nsig * p->M, p->twy, s));
     return HFD_OK;
 }

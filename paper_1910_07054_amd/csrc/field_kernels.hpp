@@ -23,174 +23,233 @@
 namespace hfd {
 
 // Rows are numbered flat over all signals (row r = signal r / ny, y = r % ny)
-// and a block takes TY consecutive rows, one wave or part of a wave per row.
-// TYO = 0 picks the default: 16 rows (or one per group of a 256-thread block),
-// halved until the tile fits in 80 KB of LDS.
+// and a block takes TY consecutive rows, one wave or part of a wave per row,
+// RPG rows one after the other where TY rows would need more than 512 threads.
+// The transposed side of a pass moves TY consecutive y of one kx: TY = 16 rows
+// (8 in FP64) are one 128-byte line.  TYO = 0 picks that, or one wave of rows
+// if that is more, halved until the tile fits in 80 KB of LDS.
 template <typename R, int LX, int TYO = 0>
 struct XPassShape {
     static constexpr int M = LX / 2;
     static constexpr int V = fft_vals(M);
     static constexpr int GT = M / V;
-    static constexpr int RS = fft_region(M) | 1;   // LDS row stride: a transform's region, odd
+    // LDS row stride = 2 x odd: 16 rows of two neighbouring kx fall on 32
+    // distinct eight-byte slots in the transposed accesses
+    static constexpr int RS = ((fft_region(M) + 1) / 4) * 4 + 2;
     static constexpr int pick_ty()
     {
         if (TYO > 0) return TYO;
-        const int ng = (GT * 16 < 256 ? 256 : (GT * 16 > 1024 ? 1024 : GT * 16)) / GT;
-        int ty = ng > 16 ? ng : 16;
+        int ty = sizeof(R) == 4 ? 16 : 8;
+        if (GT * ty < 64) ty = 64 / GT;
         while (ty > 1 && sizeof(cpx<R>) * (size_t)ty * RS > 81920) ty /= 2;
         return ty;
     }
     static constexpr int TY = pick_ty();
-    // threads: one group per row, at least one wave, at most 1024
-    static constexpr int NT0 = GT * TY;
-    static constexpr int NT = NT0 < 64 ? 64 : (NT0 > 1024 ? 1024 : NT0);
-    static constexpr int NG = NT / GT;
+    static constexpr int RPG = GT * TY > 512 ? 2 : 1;   // rows per group (GT TY <= 1024)
+    static constexpr int NG = TY / RPG;
+    static constexpr int NT = GT * NG;
     static constexpr size_t LDS = sizeof(cpx<R>) * TY * RS;
-    // waves per SIMD for two resident blocks (the register budget that allows it)
-    static constexpr int WPE = NT / 128 > 8 ? 8 : (NT / 128 < 1 ? 1 : NT / 128);
+    // waves per SIMD the register budget is cut for: 128 VGPRs hold an FP32
+    // transform of up to 16 values per lane with its twiddles, 168 an FP64 one
+    // of 8; longer ones would spill at that
+    static constexpr int WPE =
+        sizeof(R) == 4 ? (V <= 16 ? 4 : 2) : (V <= 8 ? 3 : (V <= 16 ? 2 : 1));
+    // kx pairs (k, M - k) per thread of the transposed side, 0 <= k < M/2
+    // (pair 0 is k = 0 and k = M/2, each its own mirror)
+    static constexpr int KI = V * RPG / 2, KS = NT / TY;
+    static_assert(TY % RPG == 0 && NT % TY == 0 && KI * KS == M / 2, "x pass tile");
 };
 
-// ---------------------------------------------------------------------------
-// x pass, forward: each row of nx reals (zero padded to LX) -> packed half
-// spectrum of LX/2 complex values, written transposed (y fastest).
-// A length-LX real transform is one complex transform of length LX/2 on
-// z[n] = x[2n] + i x[2n+1] followed by the even/odd split.
-// ---------------------------------------------------------------------------
-// Split of the packed real transform, per row: lane g of the row's group owns
-// the frequency pairs (k, M - k) for k = g + GT i, i < KI; their twiddles
-// exp(-2 pi i k / LX) are loaded once per lane (for the longest rows, whose
-// transform needs the registers, they are read where used).
-template <typename R, int LX>
-struct RealSplit {
-    static constexpr int M = LX / 2, GT = XPassShape<R, LX>::GT, HM = M / 2 + 1;
-    static constexpr int KI = (HM + GT - 1) / GT;
-    static constexpr bool CACHE = KI * sizeof(R) <= 32;
-    cpx<R> w[CACHE ? KI : 1];
-    const cpx<R>* tw;
-    __device__ __forceinline__ void load(int g, const cpx<R>* __restrict__ twx)
+// n / d for n < 2^32 by a multiplication (d >= 1; make(d) on the host):
+// q = (t + (n - t) / 2) >> (l - 1), t = mulhi(n, m), m = 2^32 (2^l - d) / d + 1,
+// l = ceil(log2 d)
+struct FastDiv {
+    unsigned m, s1, s2;
+    static FastDiv make(unsigned d)
     {
-        tw = twx;
-        if constexpr (CACHE) {
-#pragma unroll
-            for (int i = 0; i < KI; ++i) {
-                const int k = g + GT * i;
-                w[i] = k < HM ? twx[k] : cpx<R>{R(0), R(0)};
-            }
-        }
+        unsigned l = 0;
+        while ((1ull << l) < d) ++l;
+        return {(unsigned)((((1ull << l) - d) << 32) / d + 1), l < 1 ? l : 1u, l < 1 ? 0u : l - 1};
     }
-    __device__ __forceinline__ cpx<R> wk(int i, int k) const
+    __device__ __forceinline__ unsigned div(unsigned n) const
     {
-        if constexpr (CACHE) return w[i];
-        else return tw[k];
-    }
-    // forward: complex spectrum Z of z[n] = x[2n] + i x[2n+1] -> X[k], k < M,
-    // with X[0] and X[M] packed as X[0] + i X[M]
-    __device__ __forceinline__ void forward(cpx<R>* row, int g) const
-    {
-#pragma unroll
-        for (int i = 0; i < KI; ++i) {
-            const int k = g + GT * i;
-            if (k >= HM) continue;
-            if (k == 0) {
-                const cpx<R> z = row[0];
-                row[0] = {z.x + z.y, z.x - z.y};
-            } else if (2 * k == M) {
-                row[k] = cconj(row[k]);
-            } else {
-                const cpx<R> a = row[k], b = row[M - k];
-                const cpx<R> E = {R(0.5) * (a.x + b.x), R(0.5) * (a.y - b.y)};
-                const cpx<R> O = {R(0.5) * (a.y + b.y), R(0.5) * (b.x - a.x)};
-                const cpx<R> wO = cmul(wk(i, k), O);
-                row[k] = cadd(E, wO);
-                row[M - k] = cconj(csub(E, wO));
-            }
-        }
-    }
-    // inverse: packed half spectrum -> spectrum of z (unnormalized, twice the
-    // forward's input)
-    __device__ __forceinline__ void inverse(cpx<R>* row, int g) const
-    {
-#pragma unroll
-        for (int i = 0; i < KI; ++i) {
-            const int k = g + GT * i;
-            if (k >= HM) continue;
-            if (k == 0) {
-                const cpx<R> z = row[0];
-                row[0] = {z.x + z.y, z.x - z.y};
-            } else if (2 * k == M) {
-                const cpx<R> z = row[k];
-                row[k] = {R(2) * z.x, R(-2) * z.y};
-            } else {
-                const cpx<R> a = row[k], b = row[M - k];
-                const cpx<R> P = {a.x + b.x, a.y - b.y};   // a + conj(b)
-                const cpx<R> Qd = {a.x - b.x, a.y + b.y};  // a - conj(b)
-                const cpx<R> T = cmul(cconj(wk(i, k)), Qd);
-                row[k] = {P.x - T.y, P.y + T.x};
-                row[M - k] = {P.x + T.y, T.x - P.y};
-            }
-        }
+        const unsigned t = __umulhi(n, m);
+        return (t + ((n - t) >> s1)) >> s2;
     }
 };
 
+// Split of the packed real transform on one pair (k, M - k): the complex
+// spectrum Z of z[n] = x[2n] + i x[2n+1] against the half spectrum X of x,
+// with X[0] and X[M] packed as X[0] + i X[M]; w = exp(-2 pi i k / LX).
+// pair0: a = entry 0, b = entry M/2.
+template <typename R>
+__device__ __forceinline__ void real_split_fwd(cpx<R>& a, cpx<R>& b, cpx<R> w, bool pair0)
+{
+    const cpx<R> E = {R(0.5) * (a.x + b.x), R(0.5) * (a.y - b.y)};
+    const cpx<R> O = {R(0.5) * (a.y + b.y), R(0.5) * (b.x - a.x)};
+    const cpx<R> wO = cmul(w, O);
+    const cpx<R> p = cadd(E, wO), q = cconj(csub(E, wO));
+    const cpx<R> p0 = {a.x + a.y, a.x - a.y}, q0 = cconj(b);
+    a = pair0 ? p0 : p;
+    b = pair0 ? q0 : q;
+}
+// packed half spectrum -> spectrum of z (unnormalized, twice the forward's input)
+template <typename R>
+__device__ __forceinline__ void real_split_inv(cpx<R>& a, cpx<R>& b, cpx<R> w, bool pair0)
+{
+    const cpx<R> P = {a.x + b.x, a.y - b.y};   // a + conj(b)
+    const cpx<R> Qd = {a.x - b.x, a.y + b.y};  // a - conj(b)
+    const cpx<R> T = cmul(cconj(w), Qd);
+    const cpx<R> p = {P.x - T.y, P.y + T.x}, q = {P.x + T.y, T.x - P.y};
+    const cpx<R> p0 = {a.x + a.y, a.x - a.y}, q0 = {R(2) * b.x, R(-2) * b.y};
+    a = pair0 ? p0 : p;
+    b = pair0 ? q0 : q;
+}
+
 // ---------------------------------------------------------------------------
-// x pass, forward: each row of nx reals (zero padded to LX) -> packed half
-// spectrum of LX/2 complex values, written transposed (y fastest).
+// x pass, forward: each row of nx <= LX/2 reals (zero padded to LX) -> packed
+// half spectrum of LX/2 complex values, written transposed (y fastest).
 // A length-LX real transform is one complex transform of length LX/2 on
-// z[n] = x[2n] + i x[2n+1] followed by the even/odd split, which the row's
-// group applies to its own row.  HALF: nx <= LX/2, so z[n] is zero for
-// n >= LX/4 and the first radix pass skips that half (the field path; the
-// tensor transforms run on full rows).
+// z[n] = x[2n] + i x[2n+1] followed by the even/odd split; z[n] is zero for
+// n >= LX/4, which the first radix pass skips.  The rows' spectra meet in LDS
+// once: the split runs on the transposed side, where a thread takes the pairs
+// (k, M - k) of one row and consecutive threads consecutive rows, straight
+// into the stores.
+// Bound by the latency of its one round trip at small row counts and by HBM at
+// large ones.  All global accesses of a thread are requested together, and
+// the indices are divided out once per thread; with the split in the rows (one
+// more LDS round trip) and an index division per element the two passes of
+// 64 states of 512 x 512 x 4 took 932 + 1360 us, now 578 + 569 (2.4 GB each at
+// 4.2 TB/s; a copy runs at 4.9), those of one 256 x 256 x 8 state 9.1 + 8.7,
+// now 6.8 + 6.2.
 // ---------------------------------------------------------------------------
-template <typename R, int LX, int TYO = 0, bool HALF = true>
+template <typename R, int LX, int TYO = 0>
 __global__ __launch_bounds__((XPassShape<R, LX, TYO>::NT), (XPassShape<R, LX, TYO>::WPE)) void k_xfwd(
-    const R* __restrict__ in, cpx<R>* __restrict__ out, int nx, int ny, int nrows,
-    long long in_sig_stride, int in_row_stride, const cpx<R>* __restrict__ twx)
+    const R* __restrict__ in, cpx<R>* __restrict__ out, int nx, int ny, int nrows, FastDiv dny,
+    const cpx<R>* __restrict__ twx)
 {
     using S = XPassShape<R, LX, TYO>;
-    constexpr int M = S::M, GT = S::GT, NG = S::NG, TY = S::TY, RS = S::RS, NT = S::NT;
+    constexpr int M = S::M, V = S::V, GT = S::GT, NG = S::NG, TY = S::TY, RS = S::RS, RPG = S::RPG;
+    constexpr int KI = S::KI, KS = S::KS;
     extern __shared__ __align__(16) unsigned char smem_raw[];
     cpx<R>* sh = reinterpret_cast<cpx<R>*>(smem_raw);
     const int r0 = blockIdx.x * TY;
     const int tid = threadIdx.x, grp = tid / GT, g = tid % GT;
-    Twiddles<R, M> tw;
-    tw.load(g, twx, 2);
-    RealSplit<R, LX> split;
-    split.load(g, twx);
 
-    for (int r = grp; r < TY; r += NG) {
-        const int fr = r0 + r;
-        if (fr >= nrows) break;
-        const int sig = fr / ny, y = fr - sig * ny;
-        cpx<R>* row = sh + r * RS;
-        const R* src = in + (long long)sig * in_sig_stride + (long long)y * in_row_stride;
-        if ((nx & 1) == 0 && (in_row_stride & 1) == 0 && (in_sig_stride & 1) == 0) {
+    cpx<R> v[RPG][V];
+#pragma unroll
+    for (int q = 0; q < RPG; ++q) {
+        const int fr = r0 + grp + q * NG;
+        // rows are contiguous, so row fr starts at fr nx
+        const R* src = in + (long long)fr * nx;
+        const int lim = fr < nrows ? nx : 0;
+        if ((nx & 1) == 0) {
             // even rows: (x[2n], x[2n+1]) is one aligned 2-element load
             const cpx<R>* src2 = reinterpret_cast<const cpx<R>*>(src);
-            const int nh = nx >> 1;
-            wave_fft<R, M, false, HALF>(
-                row, g, tw,
-                [&](int pos) -> cpx<R> { return pos < nh ? src2[pos] : cpx<R>{R(0), R(0)}; },
-                [&](int pos, cpx<R> v) { row[pos] = v; });
+            const int nh = lim >> 1;
+            fft_first_loads<R, M, true>(v[q], g, [&](int pos) -> cpx<R> {
+                return pos < nh ? src2[pos] : cpx<R>{R(0), R(0)};
+            });
         } else {
-            wave_fft<R, M, false, HALF>(
-                row, g, tw,
-                [&](int pos) -> cpx<R> {
-                    const int n0 = 2 * pos;
-                    return {n0 < nx ? src[n0] : R(0), n0 + 1 < nx ? src[n0 + 1] : R(0)};
-                },
-                [&](int pos, cpx<R> v) { row[pos] = v; });
+            fft_first_loads<R, M, true>(v[q], g, [&](int pos) -> cpx<R> {
+                const int n0 = 2 * pos;
+                return {n0 < lim ? src[n0] : R(0), n0 + 1 < lim ? src[n0 + 1] : R(0)};
+            });
         }
-        wave_sync();
-        split.forward(row, g);
+    }
+    Twiddles<R, M> tw;
+    tw.load(g, twx, 2);
+    const int rb = tid % TY, kb = tid / TY;
+    cpx<R> ws[KI];
+#pragma unroll
+    for (int i = 0; i < KI; ++i) ws[i] = twx[kb + i * KS];
+#pragma unroll
+    for (int q = 0; q < RPG; ++q) {
+        cpx<R>* row = sh + (grp + q * NG) * RS;
+        wave_fft_pre<R, M, false, true>(row, g, tw, v[q], [&](int pos, cpx<R> z) { row[pos] = z; });
     }
     __syncthreads();
-    // transposed store: consecutive threads take consecutive rows of one kx
-    for (int idx = tid; idx < M * TY; idx += NT) {
-        const int r = idx % TY, kx = idx / TY;
-        const int fr = r0 + r;
-        if (fr < nrows) {
-            const int sig = fr / ny, y = fr - sig * ny;
-            out[((long long)sig * M + kx) * ny + y] = sh[r * RS + kx];
+    const int fr = r0 + rb;
+    if (fr >= nrows) return;
+    const int sig = (int)dny.div((unsigned)fr), y = fr - sig * ny;
+    cpx<R>* dst = out + (long long)sig * M * ny + y;
+    const cpx<R>* row = sh + rb * RS;
+#pragma unroll
+    for (int i = 0; i < KI; ++i) {
+        const int k = kb + i * KS;
+        const int kn = k == 0 ? M / 2 : M - k;
+        cpx<R> a = row[k], b = row[kn];
+        real_split_fwd(a, b, ws[i], k == 0);
+        dst[(long long)k * ny] = a;
+        dst[(long long)kn * ny] = b;
+    }
+}
+
+// ---------------------------------------------------------------------------
+// x pass, inverse: packed half spectrum (transposed) -> nx <= LX/2 reals per
+// row (only that half of the transform is kept).  Unnormalized; the 1/(Lx Ly)
+// is folded into the tensor.  The mirror image of k_xfwd: a thread requests
+// all its pairs (k, M - k) of one row, splits them in registers and puts them
+// into LDS, where the row's group finds its first radix pass.
+// ---------------------------------------------------------------------------
+template <typename R, int LX, int TYO = 0>
+__global__ __launch_bounds__((XPassShape<R, LX, TYO>::NT), (XPassShape<R, LX, TYO>::WPE)) void k_xinv(
+    const cpx<R>* __restrict__ in, R* __restrict__ out, int nx, int ny, int nrows, FastDiv dny,
+    const cpx<R>* __restrict__ twx)
+{
+    using S = XPassShape<R, LX, TYO>;
+    constexpr int M = S::M, GT = S::GT, NG = S::NG, TY = S::TY, RS = S::RS, RPG = S::RPG;
+    constexpr int KI = S::KI, KS = S::KS;
+    extern __shared__ __align__(16) unsigned char smem_raw[];
+    cpx<R>* sh = reinterpret_cast<cpx<R>*>(smem_raw);
+    const int r0 = blockIdx.x * TY;
+    const int tid = threadIdx.x, grp = tid / GT, g = tid % GT;
+    {
+        const int rb = tid % TY, kb = tid / TY;
+        // (rows past the end read the last one; their group returns below)
+        const int fr = r0 + rb < nrows ? r0 + rb : nrows - 1;
+        const int sig = (int)dny.div((unsigned)fr), y = fr - sig * ny;
+        const cpx<R>* src = in + (long long)sig * M * ny + y;
+        cpx<R>* row = sh + rb * RS;
+        cpx<R> a[KI], b[KI];
+#pragma unroll
+        for (int i = 0; i < KI; ++i) {
+            const int k = kb + i * KS;
+            a[i] = src[(long long)k * ny];
+            b[i] = src[(long long)(k == 0 ? M / 2 : M - k) * ny];
+        }
+#pragma unroll
+        for (int i = 0; i < KI; ++i) {
+            const int k = kb + i * KS;
+            real_split_inv(a[i], b[i], twx[k], k == 0);
+            row[k] = a[i];
+            row[k == 0 ? M / 2 : M - k] = b[i];
+        }
+    }
+    // (in FP64 the twiddles would not fit beside the pairs)
+    Twiddles<R, M> tw;
+    if constexpr (sizeof(R) == 4) tw.load(g, twx, 2);
+    __syncthreads();
+    if constexpr (sizeof(R) == 8) tw.load(g, twx, 2);
+#pragma unroll
+    for (int q = 0; q < RPG; ++q) {
+        const int fr = r0 + grp + q * NG;
+        if (fr >= nrows) break;
+        cpx<R>* row = sh + (grp + q * NG) * RS;
+        R* dst = out + (long long)fr * nx;
+        auto ld = [&](int pos) -> cpx<R> { return row[pos]; };
+        if ((nx & 1) == 0) {
+            cpx<R>* dst2 = reinterpret_cast<cpx<R>*>(dst);
+            const int nh = nx >> 1;
+            wave_fft<R, M, true, false, true>(row, g, tw, ld, [&](int pos, cpx<R> v) {
+                if (pos < nh) dst2[pos] = v;
+            });
+        } else {
+            wave_fft<R, M, true, false, true>(row, g, tw, ld, [&](int pos, cpx<R> v) {
+                const int n0 = 2 * pos;
+                if (n0 < nx) dst[n0] = v.x;
+                if (n0 + 1 < nx) dst[n0 + 1] = v.y;
+            });
         }
     }
 }
@@ -211,15 +270,13 @@ __global__ __launch_bounds__((XPassShape<double, LX, TYO>::NT), (XPassShape<doub
 {
     using R = double;
     using S = XPassShape<R, LX, TYO>;
-    constexpr int M = S::M, GT = S::GT, NG = S::NG, TY = S::TY, RS = S::RS, NT = S::NT;
+    constexpr int M = S::M, GT = S::GT, NG = S::NG, TY = S::TY, RS = S::RS;
     extern __shared__ __align__(16) unsigned char smem_raw[];
     cpx<R>* sh = reinterpret_cast<cpx<R>*>(smem_raw);
     const int r0 = blockIdx.x * TY;
     const int tid = threadIdx.x, grp = tid / GT, g = tid % GT;
     Twiddles<R, M> tw;
     tw.load(g, twx, 2);
-    RealSplit<R, LX> split;
-    split.load(g, twx);
     for (int r = grp; r < TY; r += NG) {
         const int fr = r0 + r;
         if (fr >= nrows) break;
@@ -236,81 +293,25 @@ __global__ __launch_bounds__((XPassShape<double, LX, TYO>::NT), (XPassShape<doub
         wave_fft<R, M, false>(
             row, g, tw, [&](int pos) -> cpx<R> { return {xv(2 * pos), xv(2 * pos + 1)}; },
             [&](int pos, cpx<R> v) { row[pos] = v; });
-        wave_sync();
-        split.forward(row, g);
     }
     __syncthreads();
-    for (int idx = tid; idx < (M + 1) * TY; idx += NT) {
-        const int r = idx % TY, kx = idx / TY;
-        const int fr = r0 + r;
-        if (fr < nrows) {
-            const int sig = fr / ny, y = fr - sig * ny;
-            const int c6 = sig % 6;
-            const bool xodd = (c6 == 3 || c6 == 4);
-            // column 0 holds X[0] + i X[M] (both real for an x-even row)
-            const cpx<R> z = sh[r * RS + (kx == M ? 0 : kx)];
-            const R v = xodd ? (kx == 0 || kx == M ? R(0) : z.y) : (kx == M ? z.y : z.x);
-            out[((long long)sig * (M + 1) + kx) * ny + y] = v;
-        }
-    }
-}
-
-// ---------------------------------------------------------------------------
-// x pass, inverse: packed half spectrum (transposed) -> nx reals per row.
-// Unnormalized; the 1/(Lx Ly) is folded into the tensor.  HALF: nx <= LX/2,
-// only the first half of the transform is kept.
-// ---------------------------------------------------------------------------
-template <typename R, int LX, int TYO = 0, bool HALF = true>
-__global__ __launch_bounds__((XPassShape<R, LX, TYO>::NT), (XPassShape<R, LX, TYO>::WPE)) void k_xinv(
-    const cpx<R>* __restrict__ in, R* __restrict__ out, int nx, int ny, int nrows,
-    long long out_sig_stride, int out_row_stride, const cpx<R>* __restrict__ twx)
-{
-    using S = XPassShape<R, LX, TYO>;
-    constexpr int M = S::M, GT = S::GT, NG = S::NG, TY = S::TY, RS = S::RS, NT = S::NT;
-    extern __shared__ __align__(16) unsigned char smem_raw[];
-    cpx<R>* sh = reinterpret_cast<cpx<R>*>(smem_raw);
-    const int r0 = blockIdx.x * TY;
-    const int tid = threadIdx.x, grp = tid / GT, g = tid % GT;
-    Twiddles<R, M> tw;
-    tw.load(g, twx, 2);
-    RealSplit<R, LX> split;
-    split.load(g, twx);
-    for (int idx = tid; idx < M * TY; idx += NT) {
-        const int r = idx % TY, kx = idx / TY;
-        const int fr = r0 + r;
-        cpx<R> v = {R(0), R(0)};
-        if (fr < nrows) {
-            const int sig = fr / ny, y = fr - sig * ny;
-            v = in[((long long)sig * M + kx) * ny + y];
-        }
-        sh[r * RS + kx] = v;
-    }
-    __syncthreads();
-    for (int r = grp; r < TY; r += NG) {
-        const int fr = r0 + r;
-        if (fr >= nrows) break;
-        const int sig = fr / ny, y = fr - sig * ny;
-        cpx<R>* row = sh + r * RS;
-        split.inverse(row, g);
-        wave_sync();
-        R* dst = out + (long long)sig * out_sig_stride + (long long)y * out_row_stride;
-        if ((nx & 1) == 0 && (out_row_stride & 1) == 0 && (out_sig_stride & 1) == 0) {
-            cpx<R>* dst2 = reinterpret_cast<cpx<R>*>(dst);
-            const int nh = nx >> 1;
-            wave_fft<R, M, true, false, HALF>(
-                row, g, tw, [&](int pos) -> cpx<R> { return row[pos]; },
-                [&](int pos, cpx<R> v) {
-                    if (pos < nh) dst2[pos] = v;
-                });
-        } else {
-            wave_fft<R, M, true, false, HALF>(
-                row, g, tw, [&](int pos) -> cpx<R> { return row[pos]; },
-                [&](int pos, cpx<R> v) {
-                    const int n0 = 2 * pos;
-                    if (n0 < nx) dst[n0] = v.x;
-                    if (n0 + 1 < nx) dst[n0 + 1] = v.y;
-                });
-        }
+    const int fr = r0 + tid % TY;
+    if (fr >= nrows) return;
+    const int sig = fr / ny, y = fr - sig * ny;
+    const int c6 = sig % 6;
+    const bool xodd = (c6 == 3 || c6 == 4);
+    double* dst = out + (long long)sig * (M + 1) * ny + y;
+    const cpx<R>* row = sh + (tid % TY) * RS;
+#pragma unroll
+    for (int i = 0; i < S::KI; ++i) {
+        const int k = tid / TY + i * S::KS;
+        const int kn = k == 0 ? M / 2 : M - k;
+        cpx<R> a = row[k], b = row[kn];
+        real_split_fwd(a, b, twx[k], k == 0);
+        // entry 0 holds X[0] + i X[M] (both real for an x-even row)
+        dst[(long long)k * ny] = xodd ? (k == 0 ? R(0) : a.y) : a.x;
+        dst[(long long)kn * ny] = xodd ? b.y : b.x;
+        if (k == 0) dst[(long long)M * ny] = xodd ? R(0) : a.y;
     }
 }
 

@@ -31,12 +31,10 @@ bool x_tile_supported(bool fp64, int LX, int ty);
 // (x-odd ones), which is the non-zero one
 hipError_t launch_xtab(int LX, const double* in, void* out, int nx, int ny, int nsig, const void* twx64,
                        hipStream_t s);
-hipError_t launch_xfwd(bool fp64, int LX, const void* in, void* out, int nx, int ny,
-                       long long in_sig_stride, int in_row_stride, int nsig, const void* twx,
-                       hipStream_t s, int ty = 0);
-hipError_t launch_xinv(bool fp64, int LX, const void* in, void* out, int nx, int ny,
-                       long long out_sig_stride, int out_row_stride, int nsig, const void* twx,
-                       hipStream_t s, int ty = 0);
+hipError_t launch_xfwd(bool fp64, int LX, const void* in, void* out, int nx, int ny, int nsig,
+                       const void* twx, hipStream_t s, int ty = 0);
+hipError_t launch_xinv(bool fp64, int LX, const void* in, void* out, int nx, int ny, int nsig,
+                       const void* twx, hipStream_t s, int ty = 0);
 
 // y pass on columns: forward (n_in values padded to LY) / inverse (first n_out kept)
 hipError_t launch_yfwd(bool fp64, int LY, const void* in, void* out, int n_in, long long ncols,

@@ -455,3 +455,26 @@ def test_chunked_runs_match_oracle_with_two_stacks(ny):
         for b in range(B):
             assert rel_err(h[b], refs[b]) < 1e-5, (chunk, b)
     plan.destroy()
+
+
+# ---------------------------------------------------------------------------
+# x passes: long rows (two rows per group, 16 and 32 values per lane), odd row
+# lengths, and row counts that leave a tile nearly empty
+# ---------------------------------------------------------------------------
+@pytest.mark.parametrize("fp64", [False, True])
+@pytest.mark.parametrize("nx,ny,nz", [(601, 3, 1), (1201, 2, 1), (257, 17, 1), (130, 1, 2)])
+def test_x_passes_long_and_odd_rows(nx, ny, nz, fp64):
+    wl = W.small_case(nx, ny, nz, seed=700 + nx)
+    plan = plan_for(wl, flags=hfd.HFD_FP64 if fp64 else hfd.HFD_FP32)
+    dt = np.float64 if fp64 else np.float32
+    ref = oracle.field(nx, ny, wl.dx, wl.dy, wl.z_bottom[0], wl.thickness[0],
+                       wl.m[0].astype(dt).astype(np.float64))
+    path = 0 if plan.info().fused else 1
+    for ty in (0, 4, 8, 12, 16, 24, 32):
+        try:
+            plan.set_path(1, path, ty)
+        except hfd.HFDError:
+            continue
+        h, _ = run_field(plan, wl.m)
+        assert rel_err(h[0], ref) < (1e-10 if fp64 else 1e-5), ty
+    plan.destroy()
