@@ -938,6 +938,8 @@ hfd_status run_field(hfd_plan p, const void* in, void* out, int batch, int adjoi
         mark();
     } else {
         const long long ncols = (long long)nsig * p->M;
+        void* mixed =
+            path == 1 && mix_generic_in_place(p->fp64, p->nz, p->M, p->Ly, batch) ? p->Mh : p->Hh;
         if (on()) HFD_HIP(launch_yfwd(p->fp64, p->Ly, x1, p->Mh, p->ny, ncols, p->twy, s));
         mark();
         if (on()) {
@@ -950,18 +952,16 @@ hfd_status run_field(hfd_plan p, const void* in, void* out, int batch, int adjoi
             } else if (path == 2 || path == 3) {
                 // packed column by the generic kernel, the rest batched
                 HFD_HIP(launch_mix_generic(p->fp64, p->Mh, p->Hh, p->nz, p->M, p->Ly, batch, p->Q,
-                                           p->qcs, p->qslot, p->QX, p->QY, p->lp, bpg, adjoint, 0, 1,
-                                           s));
+                                           p->qcs, p->qslot, p->QY, p->lp, bpg, adjoint, 0, 1, s));
                 HFD_HIP(launch_mix_batched(path == 3, p->Mh, p->Hh, p->nz, p->M, p->Ly, batch, p->Q,
                                            p->qcs, p->qslot, p->QY, p->lp, bpg, adjoint, s));
             } else {
-                HFD_HIP(launch_mix_generic(p->fp64, p->Mh, p->Hh, p->nz, p->M, p->Ly, batch, p->Q,
-                                           p->qcs, p->qslot, p->QX, p->QY, p->lp, bpg, adjoint, 0,
-                                           p->M, s));
+                HFD_HIP(launch_mix_generic(p->fp64, p->Mh, mixed, p->nz, p->M, p->Ly, batch, p->Q,
+                                           p->qcs, p->qslot, p->QY, p->lp, bpg, adjoint, 0, p->M, s));
             }
         }
         mark();
-        if (on()) HFD_HIP(launch_yinv(p->fp64, p->Ly, p->Hh, x1, p->ny, ncols, p->twy, s));
+        if (on()) HFD_HIP(launch_yinv(p->fp64, p->Ly, mixed, x1, p->ny, ncols, p->twy, s));
         mark();
     }
     if (on())

@@ -18,6 +18,8 @@
 //   lp     [G][2][nz]               1 / t_l and -t_l / (Lx Ly) (trace of the
 //                                   self-pair block, which fixes zz)
 #pragma once
+#include <type_traits>
+
 #include "hfd_device.hpp"
 
 namespace hfd {
@@ -955,124 +957,245 @@ __global__ __launch_bounds__((YPassShape<R, LY>::NT)) void k_yinv(const cpx<R>* 
         });
 }
 
-// Five-pass z-mixing on full spectra (any nz).  Lanes 2t' and 2t'+1 of a wave
-// take the ky points t and LY - t (t = 0: ky = 0 and LY/2), which share one
-// quadrant tensor entry; a block (one wave) takes one group of IB target
-// layers of 32 ky pairs, each lane summing over all source layers with its IB
-// targets' accumulators in registers.  One-dimensional grid, block 64.  Tiles
-// (32 ky pairs of one kx column of one state) are numbered ky tile fastest;
-// block L runs target group (L / 8) % ngrp of tile 8 ((L / 8) / ngrp) + L % 8,
-// so the ngrp blocks of one tile are 8 apart and land on the same XCD (blocks
-// are dispatched to the 8 XCDs in turn): they share the tile's spectra and
-// tensor entries in that XCD's L2.
+// One stored block (xx, yy, xy, xz, yz, and u = xx + yy - trace, so zz = -u)
+// applied to a source in the rotated components (X, Y, iZ), in which the block
+// is the real matrix [[xx, xy, xz], [xy, yy, yz], [-xz, -yz, zz]]; TR: the
+// conjugate block of the transposed pair (xz, yz negated).
+template <bool TR, typename R>
+__device__ __forceinline__ void block_real(cpx<R> (&h)[3], cpx<R> X, cpx<R> Y, cpx<R> Z, const R (&q)[5], R u)
+{
+    const R xx = q[0], yy = q[1], xy = q[2], xz = TR ? -q[3] : q[3], yz = TR ? -q[4] : q[4];
+    h[0].x = fma(xx, X.x, h[0].x); h[0].x = fma(xy, Y.x, h[0].x); h[0].x = fma(xz, Z.x, h[0].x);
+    h[0].y = fma(xx, X.y, h[0].y); h[0].y = fma(xy, Y.y, h[0].y); h[0].y = fma(xz, Z.y, h[0].y);
+    h[1].x = fma(xy, X.x, h[1].x); h[1].x = fma(yy, Y.x, h[1].x); h[1].x = fma(yz, Z.x, h[1].x);
+    h[1].y = fma(xy, X.y, h[1].y); h[1].y = fma(yy, Y.y, h[1].y); h[1].y = fma(yz, Z.y, h[1].y);
+    h[2].x = fma(-xz, X.x, h[2].x); h[2].x = fma(-yz, Y.x, h[2].x); h[2].x = fma(-u, Z.x, h[2].x);
+    h[2].y = fma(-xz, X.y, h[2].y); h[2].y = fma(-yz, Y.y, h[2].y); h[2].y = fma(-u, Z.y, h[2].y);
+}
+
+// Five-pass z-mixing on full spectra (any nz), in place where Hh = Mh.
+// A block takes one tile: 32 ky pairs of one kx column of one state, lanes l
+// and 32 + l of every wave on the ky points t and LY - t (t = 0: ky = 0 and
+// LY/2), which share one quadrant tensor entry.  The tile's spectra are staged
+// once in LDS; each wave owns IB target layers, sums over all sources with its
+// accumulators in registers, and requests the next source's entries while it
+// applies the current one's.
+// * Every entry of a layer pair is wanted by two waves, the owners of its two
+//   layers: target groups g and g' take each other's sources in the same round
+//   r (g + g' = r mod the group count), so the second request finds the line in
+//   L1 or L2.  Blocks of more than 8 waves keep their rounds in step with a
+//   barrier (64 layers: 1103 -> 995 us); smaller ones do not need it.
+// * The two halves of a wave want the same entries, so each asks for one of two
+//   targets' and halves() hands them over (10 loads for 20 entries).  That
+//   does not hold for the first ky tile (t = 0 reads two different entries) nor
+//   for the packed column (two different rows), which load every entry.
+// * Each XCD (blocks go to the 8 XCDs in turn) runs a contiguous range of tiles,
+//   the parts of a tile and the states first, then the ky tiles of a column: a
+//   tile's 128-byte slices of the (odd-length) tensor rows straddle two lines,
+//   and the states of one stack read the same entries.
+// * In the rotated components (X, sg Y, iZ), sg = -1 on the points LY - t, where
+//   xy and yz change sign, the block is the same real matrix for both points:
+//   18 FMAs and one addition per direction.
+// Bound by the stream of the tensor: per call 20 (FP64: 40) bytes per pair and
+// quadrant frequency.  256 x 256 cells, FP32: 8 / 16 / 32 layers 54 / 115 / 406 ->
+// 21 / 56 / 259 us (98, 280, 899 MB: 4.7, 5.0, 3.5 TB/s; 1.0 GB is fetched at 32
+// layers), FP64, 8 layers 74 -> 37 us (196 MB from the Infinity Cache).  Before, one
+// wave per target group read the spectra and entries of its tile on its own, 4.5
+// times what is needed at 32 layers.
 // Column 0 carries kx = 0 and Lx/2 packed as A + iB: lane p = 0 mixes A(t)
 // with the kx = 0 row and lane p = 1 B(t) with the kx = Lx/2 row, and the pair
-// repacks through a lane shuffle; the self-mirrored points t = 0 (ky = 0 and
-// LY/2) mix both parts on one lane.
-template <typename R, int IB>
-__global__ __launch_bounds__(64, 4) void k_mix_pairs(const cpx<R>* __restrict__ Mh,
-                                                    cpx<R>* __restrict__ Hh, int nz, int M, int LY,
-                                                    const R* __restrict__ Q, long long qcs,
-                                                    const int* __restrict__ qslot, int QY,
-                                                    const R* __restrict__ lp, int bpg, int adjoint,
-                                                    int kx0, int nkx, int B)
+// repacks through a lane shuffle; at the self-mirrored points t = 0 (ky = 0 and
+// LY/2) only xx, yy and zz are non-zero: the real part A takes the kx = 0 row
+// and the imaginary part B, in a second sweep of that one tile, the kx = Lx/2 row.
+// jc: layers staged at a time; parts: blocks that share a tile's target groups
+// (not in place: they all read the tile); NT: the largest block.
+template <typename R, int IB, int NT>
+__global__ __launch_bounds__(NT) void k_mix_tile(const cpx<R>* Mh, cpx<R>* Hh, int nz, int M, int LY,
+                                                 const R* __restrict__ Q, long long qcs,
+                                                 const int* __restrict__ qslot, int QY,
+                                                 const R* __restrict__ lp, int bpg, int adjoint,
+                                                 int kx0, int ntile, int B, int jc, int parts)
 {
-    const int ngrp = (nz + IB - 1) / IB;
-    const int nkyb = (LY / 2 + 31) / 32;
-    const long long L = blockIdx.x;
-    const long long r = L >> 3;
-    const long long tile = (r / ngrp) * 8 + (L & 7);
-    if (tile >= (long long)nkyb * nkx * B) return;  // padding of the last tiles
-    const int kyb = (int)(tile % nkyb);
-    const int kx = kx0 + (int)((tile / nkyb) % nkx), b = (int)(tile / ((long long)nkyb * nkx));
-    const int lane = threadIdx.x & 63, i0 = (int)(r % ngrp) * IB;
-    const int t = kyb * 32 + (lane >> 1), p = lane & 1;
-    if (t >= LY / 2) return;  // no block-level synchronization below
-    const int S = 3 * nz, geom = b / bpg;
+    static_assert(IB % 2 == 0, "targets in pairs");
+    extern __shared__ __align__(16) unsigned char smem_raw[];
+    cpx<R>* sh = reinterpret_cast<cpx<R>*>(smem_raw);  // [3][jc][64]
+    const int unit = (int)(blockIdx.x & 7) * (int)(gridDim.x >> 3) + (int)(blockIdx.x >> 3);
+    // (integer divisions run on the vector unit: back to scalars)
+    const int tile = __builtin_amdgcn_readfirstlane(unit / parts), part = unit - tile * parts;
+    if (tile >= ntile) return;
+    const int nkyb = (LY / 2 + 31) / 32, col = __builtin_amdgcn_readfirstlane(tile / B);
+    const int b = tile - col * B, ck = __builtin_amdgcn_readfirstlane(col / nkyb);
+    const int kyb = col - ck * nkyb, kx = kx0 + ck;
+    const int geom = __builtin_amdgcn_readfirstlane(b / bpg);
+    const int lane = threadIdx.x & 63, W = blockDim.x >> 6;
+    const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int t0 = kyb * 32 + (lane & 31), p = lane >> 5;
+    const bool active = t0 < LY / 2;
+    const int t = active ? t0 : 0;
+    const int ky = p == 0 ? t : (t == 0 ? LY / 2 : LY - t);
+    const int kq = p == 0 ? t : (t == 0 ? LY / 2 : t);
     const long long sst = (long long)M * LY;
-    const cpx<R>* mb = Mh + ((long long)b * S * M + kx) * LY;
-    cpx<R>* hb = Hh + ((long long)b * S * M + kx) * LY;
+    const cpx<R>* mb = Mh + ((long long)b * 3 * nz * M + kx) * LY + ky;
+    cpx<R>* hb = Hh + ((long long)b * 3 * nz * M + kx) * LY + ky;
     const R* lpg = lp + (long long)geom * 2 * nz;
     const int* sl = qslot + (long long)geom * (nz * (nz + 1) / 2);  // the stack's pair slots
-    const R* dg = lpg + nz;
+    const bool packed = kx == 0, mirror = packed && kyb == 0;
+    const R sg = (!packed && p == 1 && t != 0) ? R(-1) : R(1);
+    // a lane of the packed column reads row kx = 0 or kx = M (adjacent rows)
+    const UniformBuf<R> qb(Q + (long long)tab_row(kx, M) * qcs,
+                           __builtin_amdgcn_readfirstlane((unsigned)((packed ? 2 : 1) * qcs * sizeof(R))));
+    const int gi = part * W + w, i0 = gi * IB;   // this wave's target group
+    const bool pace = W > 8;
+    int rowbase[IB];   // pair (i, j >= i) is rowbase + j
+#pragma unroll
+    for (int k = 0; k < IB; ++k) {
+        const int i = i0 + k < nz ? i0 + k : nz - 1;
+        rowbase[k] = i * nz - i * (i - 1) / 2 - i;
+    }
 
-    // H[IB][3] += S^{ij} v_j over all sources j; row: tensor row (kx) base,
-    // kq: quadrant column, sg: sign of the ky-odd components
-    auto mix = [&](cpx<R> (&H)[IB][3], const R* row, int kq, R sg, auto in) {
-        for (int k = 0; k < IB; ++k)
-            for (int c = 0; c < 3; ++c) H[k][c] = {R(0), R(0)};
-        for (int j = 0; j < nz; ++j) {
-            const R sc = adjoint ? lpg[j] : R(1);
-            const cpx<R> X = cscale(in(0, j), sc), Y = cscale(in(1, j), sc), Z = cscale(in(2, j), sc);
+    cpx<R> H[IB][3];
+#pragma unroll
+    for (int k = 0; k < IB; ++k)
+#pragma unroll
+        for (int c = 0; c < 3; ++c) H[k][c] = {R(0), R(0)};
+    for (int step = 0; step < (mirror ? 2 : 1); ++step)
+    for (int j0 = 0; j0 < nz; j0 += jc) {
+        const int jn = nz - j0 < jc ? nz - j0 : jc;
+        if (j0 > 0 || step > 0) __syncthreads();
+        for (int lb = w * IB; lb < jn; lb += W * IB) {
+            cpx<R> z[IB][3];
+#pragma unroll
+            for (int k = 0; k < IB; ++k)
+#pragma unroll
+                for (int c = 0; c < 3; ++c)
+                    z[k][c] = mb[(c * nz + j0 + (lb + k < jn ? lb + k : jn - 1)) * sst];
 #pragma unroll
             for (int k = 0; k < IB; ++k) {
-                const int i = i0 + k;
-                if (i < nz) {
-                    const int a = i < j ? i : j, bq = i < j ? j : i;
-                    const R* q = row + (long long)sl[a * nz - a * (a - 1) / 2 + (bq - a)] * 5 * QY + kq;
-                    const R simag = i <= j ? R(1) : R(-1);  // conj for the transposed pair
-                    const R xx = q[0], yy = q[QY], xy = sg * q[2 * QY], xz = simag * q[3 * QY],
-                            yz = sg * simag * q[4 * QY];
-                    const R zz = -(xx + yy) + (i == j ? dg[i] : R(0));
-                    block_apply(H[k][0], H[k][1], H[k][2], X, Y, Z, xx, yy, zz, xy, xz, yz);
+                const int l = lb + k;
+                if (l >= jn) break;
+#pragma unroll
+                for (int c = 0; c < 3; ++c) {
+                    cpx<R> v = z[k][c];
+                    if (packed) {
+                        // A(t) = (Z(t) + conj Z(-t)) / 2 on lane 0, B(t) = (Z(t) - conj Z(-t)) / (2i) on
+                        // lane 1; the self-mirrored points take A, then iB
+                        const cpx<R> o = {__shfl_xor(v.x, 32), __shfl_xor(v.y, 32)};
+                        if (t != 0)
+                            v = p == 0 ? cpx<R>{R(0.5) * (v.x + o.x), R(0.5) * (v.y - o.y)}
+                                       : cpx<R>{R(0.5) * (o.y + v.y), R(0.5) * (v.x - o.x)};
+                        else
+                            v = step == 0 ? cpx<R>{v.x, R(0)} : cpx<R>{R(0), v.y};
+                        if (step > 0 && t != 0) v = {R(0), R(0)};
+                    }
+                    if (adjoint) v = cscale(v, lpg[j0 + l]);
+                    if (c == 1) v = cscale(v, sg);
+                    if (c == 2) v = {-v.y, v.x};
+                    sh[(c * jn + l) * 64 + lane] = v;
                 }
             }
         }
-    };
-    auto store = [&](const cpx<R> (&H)[IB][3], int ky) {
+        __syncthreads();
+        // (second sweep: the self-mirrored points read row kx = M)
+        const unsigned voff = (unsigned)(kq + (packed && ((p == 1 && t != 0) || step > 0) ? qcs : 0LL));
+
+        // the sources of this chunk in rounds of IB
+        const int nr = (jn + IB - 1) / IB;
+        int sn[IB];   // table offsets of the source to fetch next
+        auto slots = [&](int js) {
+            const int j = j0 + (js < jn ? js : jn - 1), jrow = j * nz - j * (j - 1) / 2 - j;
 #pragma unroll
-        for (int k = 0; k < IB; ++k) {
-            const int i = i0 + k;
-            if (i < nz) {
-                const R post = adjoint ? R(1) : lpg[i];
-                for (int c = 0; c < 3; ++c) hb[(c * nz + i) * sst + ky] = cscale(H[k][c], post);
+            for (int k = 0; k < IB; ++k) {
+                const int i = i0 + k < nz ? i0 + k : nz - 1;
+                sn[k] = sl[i <= j ? rowbase[k] + j : jrow + i] * 5 * QY;
             }
+        };
+        auto rounds = [&](auto split) {
+            constexpr bool SPLIT = decltype(split)::value;
+            auto fetch = [&](R (&T)[IB][5]) {
+                if constexpr (SPLIT) {
+                    // each half-wave asks for the entries of one of two targets
+#pragma unroll
+                    for (int k = 0; k < IB; k += 2) {
+                        const unsigned v = voff + (unsigned)(p == 0 ? sn[k] : sn[k + 1]);
+#pragma unroll
+                        for (int c = 0; c < 5; ++c) T[k][c] = qb.ld(v, (unsigned)(c * QY));
+                    }
+                } else {
+#pragma unroll
+                    for (int k = 0; k < IB; ++k)
+#pragma unroll
+                        for (int c = 0; c < 5; ++c) T[k][c] = qb.ld(voff, (unsigned)(sn[k] + c * QY));
+                }
+            };
+            auto apply = [&](int js, const R (&T)[IB][5]) {
+                if (js >= jn) return;
+                const int j = j0 + js;
+                const cpx<R> X = sh[js * 64 + lane], Y = sh[(jn + js) * 64 + lane],
+                             Z = sh[(2 * jn + js) * 64 + lane];
+#pragma unroll
+                for (int k = 0; k < IB; k += 2) {
+                    R q[2][5];
+#pragma unroll
+                    for (int c = 0; c < 5; ++c) {
+                        if constexpr (SPLIT) {
+                            halves(T[k][c], q[0][c], q[1][c]);
+                        } else {
+                            q[0][c] = T[k][c];
+                            q[1][c] = T[k + 1][c];
+                        }
+                    }
+#pragma unroll
+                    for (int e = 0; e < 2; ++e) {
+                        const int i = i0 + k + e;
+                        R u = q[e][0] + q[e][1];
+                        if (i == j) u -= lpg[nz + i];
+                        if (i > j) block_real<true>(H[k + e], X, Y, Z, q[e], u);
+                        else block_real<false>(H[k + e], X, Y, Z, q[e], u);
+                    }
+                }
+            };
+            R T[2][IB][5];
+            int J = gi % nr;
+            J = __builtin_amdgcn_readfirstlane(J == 0 ? 0 : nr - J);   // round 0: group -gi mod nr
+            slots(J * IB);
+            fetch(T[0]);
+            slots(J * IB + 1);
+            for (int r = 0; r < nr; ++r) {
+                const int Jn = J + 1 == nr ? 0 : J + 1;
+                if (pace) __builtin_amdgcn_s_barrier();
+#pragma unroll
+                for (int k = 0; k < IB; ++k) {
+                    // (the last round fetches its successor's first source, unused)
+                    fetch(T[(k + 1) % 2]);
+                    slots(k + 2 < IB ? J * IB + k + 2 : Jn * IB + (k + 2 - IB));
+                    apply(J * IB + k, T[k % 2]);
+                }
+                J = Jn;
+            }
+        };
+        if (kyb != 0 && !packed) rounds(std::true_type{});
+        else rounds(std::false_type{});
+    }
+    if (mirror) __syncthreads();  // (the second sweep read the tile again)
+    // back to (X, Y, Z), scaled by 1/t (in place: only this block reads its
+    // tile, and every layer has been staged)
+#pragma unroll
+    for (int k = 0; k < IB; ++k) {
+        const int i = i0 + k;
+        if (i >= nz) break;
+        const R post = adjoint ? R(1) : lpg[i];
+        const cpx<R> o[3] = {cscale(H[k][0], post), cscale(H[k][1], sg * post),
+                             cpx<R>{post * H[k][2].y, -post * H[k][2].x}};
+#pragma unroll
+        for (int c = 0; c < 3; ++c) {
+            cpx<R> v = o[c];
+            if (packed) {
+                // W(t) = HA + i HB on lane 0, W(-t) = conj(HA) + i conj(HB) on lane 1
+                const cpx<R> e = {__shfl_xor(v.x, 32), __shfl_xor(v.y, 32)};
+                if (t != 0) v = p == 0 ? cpx<R>{v.x - e.y, v.y + e.x} : cpx<R>{e.x + v.y, v.x - e.y};
+            }
+            if (active) hb[(c * nz + i) * sst] = v;
         }
-    };
-    cpx<R> H[IB][3];
-    if (kx != 0) {
-        const int ky = p == 0 ? t : (t == 0 ? LY / 2 : LY - t);
-        const int kq = p == 0 ? t : (t == 0 ? LY / 2 : t);
-        const R sg = (p == 1 && t != 0) ? R(-1) : R(1);
-        mix(H, Q + tab_row(kx, M) * qcs, kq, sg,
-            [&](int c, int j) { return mb[(c * nz + j) * sst + ky]; });
-        store(H, ky);
-    } else if (t != 0) {
-        // A(t) = (Z(t) + conj Z(-t)) / 2 on lane 0, B(t) = (Z(t) - conj Z(-t)) / (2i) on lane 1
-        const int k1 = t, k2 = LY - t;
-        mix(H, Q + (p == 0 ? 0 : tab_row(M, M)) * qcs, t, R(1), [&](int c, int j) {
-            const cpx<R> z1 = mb[(c * nz + j) * sst + k1], z2 = mb[(c * nz + j) * sst + k2];
-            return p == 0 ? cpx<R>{R(0.5) * (z1.x + z2.x), R(0.5) * (z1.y - z2.y)}
-                          : cpx<R>{R(0.5) * (z1.y + z2.y), R(0.5) * (z2.x - z1.x)};
-        });
-        // W(t) = HA + i HB on lane 0, W(-t) = conj(HA) + i conj(HB) on lane 1
-#pragma unroll
-        for (int k = 0; k < IB; ++k)
-#pragma unroll
-            for (int c = 0; c < 3; ++c) {
-                const cpx<R> o = {__shfl_xor(H[k][c].x, 1), __shfl_xor(H[k][c].y, 1)};
-                const cpx<R> A = p == 0 ? H[k][c] : o, Bv = p == 0 ? o : H[k][c];
-                H[k][c] = p == 0 ? cpx<R>{A.x - Bv.y, A.y + Bv.x} : cpx<R>{A.x + Bv.y, Bv.x - A.y};
-            }
-        store(H, p == 0 ? k1 : k2);
-    } else {
-        // ky = 0 (lane 0) or LY/2 (lane 1), each its own mirror: A = Re Z, B = Im Z;
-        // the point receives A' first and then A' + i B'
-        const int kp = p == 0 ? 0 : LY / 2;
-        mix(H, Q, kp, R(1), [&](int c, int j) { return cpx<R>{mb[(c * nz + j) * sst + kp].x, R(0)}; });
-        cpx<R> keep[IB][3];
-#pragma unroll
-        for (int k = 0; k < IB; ++k)
-#pragma unroll
-            for (int c = 0; c < 3; ++c) keep[k][c] = H[k][c];
-        mix(H, Q + tab_row(M, M) * qcs, kp, R(1),
-            [&](int c, int j) { return cpx<R>{mb[(c * nz + j) * sst + kp].y, R(0)}; });
-#pragma unroll
-        for (int k = 0; k < IB; ++k)
-#pragma unroll
-            for (int c = 0; c < 3; ++c)
-                H[k][c] = {keep[k][c].x - H[k][c].y, keep[k][c].y + H[k][c].x};
-        store(H, kp);
     }
 }
 

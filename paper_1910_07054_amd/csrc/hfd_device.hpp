@@ -74,6 +74,24 @@ struct UniformBuf {
     }
 };
 
+// a = the lower half-wave's v, b = the upper one's, in both halves
+// (lane l gets the value of lane l % 32, or 32 + l % 32)
+__device__ __forceinline__ void halves(float v, float& a, float& b)
+{
+    const unsigned u = __builtin_bit_cast(unsigned, v);
+    const auto r = __builtin_amdgcn_permlane32_swap(u, u, false, false);
+    a = __builtin_bit_cast(float, (unsigned)r[0]);
+    b = __builtin_bit_cast(float, (unsigned)r[1]);
+}
+__device__ __forceinline__ void halves(double v, double& a, double& b)
+{
+    const unsigned long long u = __builtin_bit_cast(unsigned long long, v);
+    const auto lo = __builtin_amdgcn_permlane32_swap((unsigned)u, (unsigned)u, false, false);
+    const auto hi = __builtin_amdgcn_permlane32_swap((unsigned)(u >> 32), (unsigned)(u >> 32), false, false);
+    a = __builtin_bit_cast(double, ((unsigned long long)hi[0] << 32) | lo[0]);
+    b = __builtin_bit_cast(double, ((unsigned long long)hi[1] << 32) | lo[1]);
+}
+
 // values per lane for a transform of length L
 __host__ __device__ constexpr int fft_vals(int L) { return L <= 8 ? L : (L <= 512 ? 8 : L / 64); }
 

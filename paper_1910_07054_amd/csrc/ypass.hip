@@ -67,39 +67,64 @@ hipError_t launch_yinv(bool fp64, int LY, const void* in, void* out, int n_out, 
     HFD_Y_CASES(yinv_t, float, in, out, n_out, ncols, twy, s)
 }
 
-template <int IB>
-static hipError_t mix_pairs_t(bool fp64, const void* Mh, void* Hh, int nz, int M, int LY, int B,
-                              const void* Q, long long qcs, const int* qslot, int QY, const void* lp,
-                              int bpg, int adjoint, int kx0, int nkx, hipStream_t s)
+// Blocks that share a tile of the mixing kernel: more than one where the tiles
+// alone leave the chip short of blocks (below 512, two per CU; 64 x 64 x 60 in
+// FP64, 128 tiles: 425 us with one block of 15 waves each, 136 with 4 of 8) or
+// where a block of NT threads does not hold all target groups.
+static int mix_parts(int ngrp, int max_waves, long long tiles)
 {
-    const int ngrp = (nz + IB - 1) / IB;
-    const long long tiles = (long long)((LY / 2 + 31) / 32) * nkx * B;
-    const long long nblk = (tiles + 7) / 8 * 8 * ngrp;
-    if (nblk > 0x7fffffffLL) return hipErrorInvalidValue;
-    dim3 grid((unsigned)nblk);
-    if (fp64)
-        hipLaunchKernelGGL((k_mix_pairs<double, IB>), grid, dim3(64), 0, s,
-                           (const cpx<double>*)Mh, (cpx<double>*)Hh, nz, M, LY, (const double*)Q, qcs,
-                           qslot, QY, (const double*)lp, bpg, adjoint, kx0, nkx, B);
-    else
-        hipLaunchKernelGGL((k_mix_pairs<float, IB>), grid, dim3(64), 0, s,
-                           (const cpx<float>*)Mh, (cpx<float>*)Hh, nz, M, LY, (const float*)Q, qcs,
-                           qslot, QY, (const float*)lp, bpg, adjoint, kx0, nkx, B);
+    int parts = 1;
+    while ((ngrp + parts - 1) / parts > max_waves || (tiles * parts < 512 && ngrp > 2 * parts)) ++parts;
+    const int waves = (ngrp + parts - 1) / parts;
+    return (ngrp + waves - 1) / waves;
+}
+
+// Two target layers per wave in blocks of up to 8 waves; above 32 layers in
+// FP32 four in blocks of up to 16, which reads the tile once (64 layers: 979
+// against 1106 us; 32 layers: 265 against 259).
+static bool mix_wide(bool fp64, int nz) { return !fp64 && nz > 32; }
+
+static long long mix_tiles(int LY, int nkx, int B) { return (long long)((LY / 2 + 31) / 32) * nkx * B; }
+
+bool mix_generic_in_place(bool fp64, int nz, int M, int LY, int B)
+{
+    const bool wide = mix_wide(fp64, nz);
+    const int ib = wide ? 4 : 2;
+    return mix_parts((nz + ib - 1) / ib, wide ? 16 : 8, mix_tiles(LY, M, B)) == 1;
+}
+
+template <typename R, int IB, int NT>
+static hipError_t mix_tile_t(const void* Mh, void* Hh, int nz, int M, int LY, int B, const void* Q,
+                             long long qcs, const int* qslot, int QY, const void* lp, int bpg, int adjoint,
+                             int kx0, int nkx, hipStream_t s)
+{
+    const long long tiles = mix_tiles(LY, nkx, B);
+    const int ngrp = (nz + IB - 1) / IB, parts = mix_parts(ngrp, NT / 64, tiles);
+    const int waves = (ngrp + parts - 1) / parts;
+    const long long nblk = (tiles * parts + 7) / 8 * 8;
+    if (nblk > 0x7fffffffLL || (parts > 1 && Mh == Hh)) return hipErrorInvalidValue;
+    // up to 96 KB of staged spectra (64 layers in FP32, 32 in FP64); more in chunks
+    const int per = 3 * 64 * (int)sizeof(cpx<R>), chunks = (nz * per + 98303) / 98304;
+    const int jc = (nz + chunks - 1) / chunks;
+    const size_t lds = (size_t)jc * per;
+    const hipError_t e = ensure_lds_limit((const void*)k_mix_tile<R, IB, NT>, lds > 65536 ? 98304 : 0);
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL((k_mix_tile<R, IB, NT>), dim3((unsigned)nblk), dim3(64 * waves), lds, s,
+                       (const cpx<R>*)Mh, (cpx<R>*)Hh, nz, M, LY, (const R*)Q, qcs, qslot, QY, (const R*)lp,
+                       bpg, adjoint, kx0, (int)tiles, B, jc, parts);
     return hipGetLastError();
 }
 
-// 4 target layers per lane up to 15 layers, 2 from 16 on (measured at 32 layers:
-// 0.396 ms against 0.421 ms for 4 and 0.541 ms for 8; at 4 layers 4 is
-// slightly ahead)
 hipError_t launch_mix_generic(bool fp64, const void* Mh, void* Hh, int nz, int M, int LY, int B,
-                              const void* Q, long long qcs, const int* qslot, int QX, int QY,
-                              const void* lp, int bpg, int adjoint, int kx0, int nkx, hipStream_t s)
+                              const void* Q, long long qcs, const int* qslot, int QY, const void* lp,
+                              int bpg, int adjoint, int kx0, int nkx, hipStream_t s)
 {
-    (void)QX;
     if (nkx <= 0) return hipSuccess;
-    if (nz >= 16)
-        return mix_pairs_t<2>(fp64, Mh, Hh, nz, M, LY, B, Q, qcs, qslot, QY, lp, bpg, adjoint, kx0, nkx, s);
-    return mix_pairs_t<4>(fp64, Mh, Hh, nz, M, LY, B, Q, qcs, qslot, QY, lp, bpg, adjoint, kx0, nkx, s);
+    if (fp64)
+        return mix_tile_t<double, 2, 512>(Mh, Hh, nz, M, LY, B, Q, qcs, qslot, QY, lp, bpg, adjoint, kx0, nkx, s);
+    if (mix_wide(fp64, nz))
+        return mix_tile_t<float, 4, 1024>(Mh, Hh, nz, M, LY, B, Q, qcs, qslot, QY, lp, bpg, adjoint, kx0, nkx, s);
+    return mix_tile_t<float, 2, 512>(Mh, Hh, nz, M, LY, B, Q, qcs, qslot, QY, lp, bpg, adjoint, kx0, nkx, s);
 }
 
 }  // namespace hfd

@@ -478,3 +478,32 @@ def test_x_passes_long_and_odd_rows(nx, ny, nz, fp64):
         h, _ = run_field(plan, wl.m)
         assert rel_err(h[0], ref) < (1e-10 if fp64 else 1e-5), ty
     plan.destroy()
+
+
+# ---------------------------------------------------------------------------
+# Five-pass mixing at the edges of its target groups, blocks and staged chunks,
+# with more than one ky tile per column, field and transpose
+# ---------------------------------------------------------------------------
+@pytest.mark.parametrize("fp64", [False, True])
+@pytest.mark.parametrize("nz", [1, 3, 17, 33])
+def test_split_pass_mixing_at_group_edges(nz, fp64):
+    import torch
+    nx, ny = 5, 70
+    wl = W.small_case(nx, ny, nz, seed=800 + nz, batch=2)
+    plan = plan_for(wl, flags=(hfd.HFD_FP64 if fp64 else hfd.HFD_FP32) | hfd.HFD_SPLIT_PASSES)
+    dt = np.float64 if fp64 else np.float32
+    m = wl.m.astype(dt)
+    rng = np.random.default_rng(nz)
+    smp = np.stack([rng.integers(0, nz, 24), rng.integers(0, ny, 24), rng.integers(0, nx, 24)], axis=1)
+    md = torch.from_numpy(m).cuda()
+    h = plan.field(md).cpu().numpy()
+    gm, _ = plan.vjp(None, md, want_t=False)
+    gm = gm.cpu().numpy()
+    for b in range(2):
+        for got, transpose in ((h, False), (gm, True)):
+            ref = oracle.field(nx, ny, wl.dx, wl.dy, wl.z_bottom[0], wl.thickness[0],
+                               m[b].astype(np.float64), samples=smp, transpose=transpose)
+            val = got[b][:, smp[:, 0], smp[:, 1], smp[:, 2]].T
+            err = np.abs(val - ref).max() / np.linalg.norm(ref, axis=1).max()
+            assert err < (1e-10 if fp64 else 1e-5), (b, transpose, err)
+    plan.destroy()
