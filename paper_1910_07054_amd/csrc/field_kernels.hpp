@@ -35,9 +35,9 @@ struct XPassShape {
     static constexpr int M = LX / 2;
     static constexpr int V = fft_vals(M);
     static constexpr int GT = M / V;
-    // LDS row stride = 2 x odd: 16 rows of two neighbouring kx fall on 32
-    // distinct eight-byte slots in the transposed accesses
-    static constexpr int RS = ((fft_region(M) + 1) / 4) * 4 + 2;
+    // odd LDS row stride: the transposed accesses take 16 rows of one kx from
+    // 16 different slots
+    static constexpr int RS = fft_region(M) | 1;
     static constexpr int pick_ty()
     {
         if (TYO > 0) return TYO;

@@ -4,9 +4,9 @@
 // One FFT of length L is owned by a group of GT = L / V lanes of a single
 // 64-wide wavefront; every lane holds V complex values in registers.  Passes
 // use radix 8 (4 or 2 for the remainder).  Between passes the group exchanges
-// data through its own LDS region of fft_region(L) slots (L values with one
-// padding slot per eight, see lds_pad); because the group never spans two
-// wavefronts, no workgroup barrier is needed inside a transform.
+// data through its own LDS region of fft_region(L) slots (see Exchange);
+// because the group never spans two wavefronts, no workgroup barrier is needed
+// inside a transform.
 #pragma once
 #include <hip/hip_runtime.h>
 #include <stdint.h>
@@ -193,16 +193,29 @@ __device__ __forceinline__ void dft_half_in(cpx<R>* v)
     }
 }
 
-// LDS slot of element `pos` in the intermediate passes of a transform: one
-// padding slot after every eight elements, so a transform of length L uses
-// fft_region(L) slots.  The writes of a radix-8 pass go to positions 8j + r
-// (first pass, lane j) and 64q + 8r + k (later passes, lane j = 8q + k); in
-// natural order a half-wave's writes fall on 4 or 8 of the 32 eight-byte bank
-// slots, padded on 32 distinct ones.  A lane's positions differ by multiples
-// of 8 (or by r < 8 from a multiple of 8 in the first pass), so their padded
-// slots differ by compile-time constants and cost no address arithmetic.
+// LDS slots of the values between two passes.  A ds access of 8 bytes per
+// lane serves 16 consecutive lanes at a time from 16 eight-byte slots, one of 16
+// bytes 8 lanes from 8 (measured: 4.2 clocks per wave where every group's slots
+// differ modulo 16, 8.1 where two lanes share one).  A pass that follows NS
+// finished points writes pos = 8 j + r (first pass, lane j) or pos = 64 q + 8 r + k
+// (NS = 8, j = 8 q + k), the next one reads consecutive positions.  The exchange after
+// each pass has a layout of its own, slot(pos) = pos + (pos >> SHIFT) MULT:
+//   8-byte values, NS = 1: pos + pos/16 (writes 8 (j & 1) + j / 2 mod 16, reads aligned runs)
+//   8-byte values, NS = 8: pos + 8 (pos/64) (writes k + 8 q mod 16)
+//   NS > 8: as they are (both sides are runs of at least 16)
+//   16-byte values: pos + pos/8 (writes 9 j and k mod 8).
+// With pos + pos/8 for both sizes the reads of 8-byte values took twice as long.
+// A lane's positions differ by constants that do not carry into pos >> SHIFT, so
+// their slots differ by compile-time constants and cost no address arithmetic.
+// A transform of length L uses fft_region(L) slots.
+template <typename R, int NS>
+struct Exchange {
+    static constexpr bool WIDE = sizeof(R) == 8;
+    static constexpr int SHIFT = WIDE ? 3 : (NS == 1 ? 4 : 6);
+    static constexpr int MULT = WIDE ? 1 : (NS == 1 ? 1 : (NS == 8 ? 8 : 0));
+    __host__ __device__ static constexpr int slot(int pos) { return pos + (pos >> SHIFT) * MULT; }
+};
 __host__ __device__ constexpr int fft_region(int L) { return L + (L >> 3); }
-__device__ __forceinline__ int lds_pad(int pos) { return pos + (pos >> 3); }
 
 // --- Stockham engine -------------------------------------------------------
 // X[k] = sum_n x[n] exp(-+2 pi i n k / L) (unnormalized in both directions).
@@ -269,8 +282,9 @@ struct Twiddles {
 // first pass neither loads nor transforms them.  HOUT: only the output
 // positions 0 .. L/2-1 are wanted (cropped result): the last pass stores only
 // those, and what feeds nothing else is not computed.
+// PREV: the finished points of the pass before the last one (layout of its exchange).
 template <typename R, int L, int V, bool INV, int NS, int OFF, bool PRE = false, bool HIN = false,
-          bool HOUT = false, class Load, class Store>
+          bool HOUT = false, int PREV = 1, class Load, class Store>
 __device__ __forceinline__ void fft_pass(cpx<R> (&v)[V], cpx<R>* sh, int g, const cpx<R>* w,
                                          Load& load, Store& store)
 {
@@ -282,11 +296,14 @@ __device__ __forceinline__ void fft_pass(cpx<R> (&v)[V], cpx<R>* sh, int g, cons
     constexpr bool LAST = P::LAST;
     constexpr bool HALF_IN = FIRST && HIN;
     static_assert(L % (NS * RAD) == 0, "radix schedule");
+    using XIn = Exchange<R, PREV>;
+    using XOut = Exchange<R, NS>;
     static_assert(FIRST || STRIDE % 8 == 0, "later passes read at multiples of 8");
+    static_assert(LAST || RAD >= 8, "exchange layouts are for passes of radix 8 and 16");
 #pragma unroll
     for (int u = 0; u < NB; ++u) {
         const int j = g + GT * u;
-        const int pj = lds_pad(j);
+        const int pj = XIn::slot(j);
 #pragma unroll
         for (int r = 0; r < RAD; ++r) {
             if constexpr (FIRST) {
@@ -299,7 +316,7 @@ __device__ __forceinline__ void fft_pass(cpx<R> (&v)[V], cpx<R>* sh, int g, cons
                 }
                 if constexpr (!PRE) v[u * RAD + r] = load(j + r * STRIDE);
             } else {
-                v[u * RAD + r] = sh[pj + r * (STRIDE + STRIDE / 8)];
+                v[u * RAD + r] = sh[pj + XIn::slot(r * STRIDE)];
             }
         }
     }
@@ -322,22 +339,21 @@ __device__ __forceinline__ void fft_pass(cpx<R> (&v)[V], cpx<R>* sh, int g, cons
         const int j = g + GT * u;
         const int k = j & (NS - 1);
         const int base = (j - k) * RAD + k;
-        const int pb = lds_pad(base);
+        const int pb = XOut::slot(base);
 #pragma unroll
         for (int r = 0; r < RAD; ++r) {
             if constexpr (LAST) {
                 // positions base + r NS >= L/2 exactly when r >= RAD/2
                 if (!HOUT || r < RAD / 2) store(base + r * NS, v[u * RAD + r]);
             } else {
-                // first pass: (base & 7) + r < 8, so the padded slot is pb + r
-                sh[pb + r * (NS + NS / 8)] = v[u * RAD + r];
+                sh[pb + XOut::slot(r * NS)] = v[u * RAD + r];
             }
         }
     }
     if constexpr (!LAST) {
         wave_sync();
         constexpr int here = NS > 1 ? NB * (RAD - 1) : 0;
-        fft_pass<R, L, V, INV, P::NEXT, OFF + here, false, false, HOUT>(v, sh, g, w, load, store);
+        fft_pass<R, L, V, INV, P::NEXT, OFF + here, false, false, HOUT, NS>(v, sh, g, w, load, store);
     }
 }
 
