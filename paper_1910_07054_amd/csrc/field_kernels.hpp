@@ -539,16 +539,16 @@ struct FusedShape {
 // ---------------------------------------------------------------------------
 // Body of the fused y pass for column kx of state b (stack geom); the
 // kernels below launch it on a grid (M, states per stack, stacks).
-template <typename R, int LY, int NZMAX, bool ADJ>
+template <typename R, int LY, int NZMAX, bool ADJ, int NT>
 __device__ __forceinline__ void ymix_column(int kx, int b, int geom, cpx<R>* __restrict__ X,
                                             int ny, int nz, int M, const R* __restrict__ Q,
                                             long long qcs, const int* __restrict__ qslot, int QY,
                                             const R* __restrict__ lp,
                                             const cpx<R>* __restrict__ twy)
 {
-    constexpr int NT = FusedShape<LY>::NT;
     constexpr int V = fft_vals(LY), GT = LY / V, NG = NT / GT;
     constexpr int LYP = fft_region(LY);  // LDS slots per signal
+    static_assert(NT >= LY, "one thread per frequency");
     extern __shared__ __align__(16) unsigned char smem_raw[];
     cpx<R>* sh = reinterpret_cast<cpx<R>*>(smem_raw);
     const int S = 3 * nz;
@@ -700,38 +700,33 @@ __global__ __launch_bounds__(FusedShape<LY>::NT) void k_ymix_fused(
     const cpx<R>* __restrict__ twy)
 {
     const int geom = blockIdx.z;
-    ymix_column<R, LY, NZMAX, ADJ>(blockIdx.x, geom * bpg + blockIdx.y, geom, X, ny, nz, M, Q, qcs,
+    ymix_column<R, LY, NZMAX, ADJ, FusedShape<LY>::NT>(blockIdx.x, geom * bpg + blockIdx.y, geom, X, ny, nz, M, Q, qcs,
                                    qslot, QY, lp, twy);
 }
 
 // ---------------------------------------------------------------------------
 // Fused y pass for a stack of exactly NZ layers (single precision, 256-, 512-
-// or 1024-point columns, 512 threads): the same three phases as ymix_column, with every loop over
-// layers and layer pairs unrolled.  A lane's 3 NZ input values sit in
+// or 1024-point columns): the same three phases as ymix_column, with every loop
+// over layers and layer pairs unrolled.  A lane's 3 NZ input values sit in
 // registers for the whole mixing, which walks the NZ (NZ + 1) / 2 stored pairs
 // in order (i, j >= i) and applies each block both ways; the tensor entries
 // are plain loads that the compiler schedules ahead of their use.  The column
 // spectra are read and written through buffer descriptors whose size is the
 // column's ny values: the zero padding of the forward transform and the crop
 // of the inverse come from the descriptor's range check.  Column 0 (the packed
-// kx = 0 and Lx/2 columns) runs ymix_column (512-point columns) or a
+// kx = 0 and Lx/2 columns) runs ymix_column (up to 512-point columns) or a
 // separate k_ymix_fused launch (1024-point columns).
+// NT = 512, 8 waves of up to 256 VGPRs; 256 for short columns in many blocks
+// (see fused_exact_a).
 // ---------------------------------------------------------------------------
-template <int LY>
-struct ExactShape {
-    static constexpr int NT = 512;  // 8 waves at any column length: 256 VGPRs per lane
-};
-
-template <typename R, int LY, int NZ, bool ADJ, int PRE = 0>
-__global__ __launch_bounds__(ExactShape<LY>::NT) void k_ymix_fused_nz(
+template <typename R, int LY, int NZ, bool ADJ, int NT>
+__global__ __launch_bounds__(NT) void k_ymix_fused_nz(
     cpx<R>* __restrict__ X, int ny, int M, const R* __restrict__ Q, long long qcs,
     const int* __restrict__ qslot, int QY, const R* __restrict__ lp, int bpg,
     const cpx<R>* __restrict__ twy)
 {
-    constexpr int NT = ExactShape<LY>::NT;
     constexpr int V = fft_vals(LY), GT = LY / V, NG = NT / GT;
     constexpr int S = 3 * NZ, P = NZ * (NZ + 1) / 2;
-    constexpr int TPL = LY / NT;           // frequency pairs per lane pair
     constexpr int LYP = fft_region(LY);    // LDS slots per signal
     constexpr int NR = (S + NG - 1) / NG;  // signals per wave, at most
     // one transform per wavefront (512- and 1024-point columns), or two
@@ -742,11 +737,11 @@ __global__ __launch_bounds__(ExactShape<LY>::NT) void k_ymix_fused_nz(
     // 512-point columns: block 0 runs the packed column 0 with the generic
     // body (one thread per frequency, as here); longer columns leave column 0
     // to a separate launch of k_ymix_fused and start at kx = 1
-    constexpr bool OWN_COL0 = LY <= NT;
+    constexpr bool OWN_COL0 = LY <= 512;
     const int kx = blockIdx.x + (OWN_COL0 ? 0 : 1), geom = blockIdx.z, b = geom * bpg + blockIdx.y;
     if constexpr (OWN_COL0) {
         if (kx == 0) {
-            ymix_column<R, LY, NZ, ADJ>(0, b, geom, X, ny, NZ, M, Q, qcs, qslot, QY, lp, twy);
+            ymix_column<R, LY, NZ, ADJ, NT>(0, b, geom, X, ny, NZ, M, Q, qcs, qslot, QY, lp, twy);
             return;
         }
     }
@@ -759,8 +754,6 @@ __global__ __launch_bounds__(ExactShape<LY>::NT) void k_ymix_fused_nz(
     const int p = tid & 1;
     const int* sl = qslot + geom * P;  // the stack's pair slots (scalar loads)
     const UniformBuf<R> qb(Q + (long long)tab_row(kx, M) * qcs, (unsigned)(qcs * sizeof(R)));
-    static_assert(PRE == 0 || TPL == 1, "tensor prefetch for one frequency pair per lane");
-    R qpre[PRE > 0 ? PRE : 1][5];
 
     // forward transforms: the inputs of all of this wave's signals are
     // requested first, then transformed one after the other
@@ -789,16 +782,6 @@ __global__ __launch_bounds__(ExactShape<LY>::NT) void k_ymix_fused_nz(
                     });
                 }
             }
-        }
-        // the first PRE tensor pairs are requested behind the column values
-        // (the wait counter is in order), to arrive while the transforms run
-        {
-            const int t = tid >> 1, kq = p == 0 ? t : (t == 0 ? LY / 2 : t);
-#pragma unroll
-            for (int u = 0; u < PRE; ++u)
-#pragma unroll
-                for (int c = 0; c < 5; ++c)
-                    qpre[u][c] = qb.ld((unsigned)kq, (unsigned)((sl[u] * 5 + c) * QY));
         }
 #pragma unroll
         for (int r = 0; r < NR; ++r) {
@@ -835,11 +818,7 @@ __global__ __launch_bounds__(ExactShape<LY>::NT) void k_ymix_fused_nz(
 #pragma unroll
                 for (int j = i; j < NZ; ++j) {
                     const int u = i * NZ - i * (i - 1) / 2 + (j - i);
-                    auto q = [&](int c) -> R {
-                        if constexpr (PRE > 0)
-                            if (u < PRE) return qpre[u < PRE ? u : 0][c];
-                        return qb.ld((unsigned)kq, (unsigned)((sl[u] * 5 + c) * QY));
-                    };
+                    auto q = [&](int c) -> R { return qb.ld((unsigned)kq, (unsigned)((sl[u] * 5 + c) * QY)); };
                     const R xx = q(0), yy = q(1), xy = sg * q(2), xz = q(3), yz = sg * q(4);
                     R zz = -(xx + yy);
                     if (i == j) {

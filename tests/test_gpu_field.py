@@ -507,3 +507,32 @@ def test_split_pass_mixing_at_group_edges(nz, fp64):
             err = np.abs(val - ref).max() / np.linalg.norm(ref, axis=1).max()
             assert err < (1e-10 if fp64 else 1e-5), (b, transpose, err)
     plan.destroy()
+
+
+# ---------------------------------------------------------------------------
+# Exact-layer kernel at 256-point columns with enough blocks for 256-thread
+# blocks (from 512 on: here 4 or 5 states of 64 x-frequencies, two stacks)
+# ---------------------------------------------------------------------------
+@pytest.mark.parametrize("nz", [1, 2, 5, 8, 10])
+def test_exact_kernel_256_point_columns_many_blocks(nz):
+    import torch
+    nx, ny, B = 45, 67, 10
+    wl = W.small_case(nx, ny, nz, seed=900 + nz, batch=B)
+    t = np.repeat(wl.thickness, 2, axis=0)
+    t[1, -1] *= 1.25                      # the second stack differs in its top layer
+    zb = np.repeat(wl.z_bottom, 2, axis=0)
+    plan = hfd.Plan(nx, ny, wl.dx, wl.dy, t, zb, batch_max=B)
+    m = torch.from_numpy(wl.m.astype(np.float32)).cuda()
+    h = plan.field(m)
+    gm, _ = plan.vjp(None, m, want_t=False)
+    plan.set_fused(B, 0, True)            # run-time layer-count kernel
+    hg = plan.field(m)
+    gg, _ = plan.vjp(None, m, want_t=False)
+    for got, ref in ((h, hg), (gm, gg)):
+        err = float((got - ref).abs().max() / ref.abs().max())
+        assert err < 2e-6, err
+    for b in (0, B - 1):
+        g = b // (B // 2)
+        ref = oracle.field(nx, ny, wl.dx, wl.dy, zb[g], t[g], wl.m[b].astype(np.float32).astype(np.float64))
+        assert rel_err(h[b].cpu().numpy(), ref) < 1e-5, b
+    plan.destroy()
