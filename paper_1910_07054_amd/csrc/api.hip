@@ -182,6 +182,7 @@ struct hfd_plan_s {
     void* D = nullptr;          // [QX][nzeta_max][6][QY] plan precision, one offset table
     int* itab = nullptr;        // [G][itab_stride] interface positions and D slots (k_tgrad)
     int itab_stride = 0;
+    int ni_max = 0;             // most interface positions of a stack
     double* zeta_dev = nullptr; // [tables][nzeta_max]
     int nzeta_max = 0;
     std::vector<int> nzeta;     // per table (one shared table when stored, else per group)
@@ -193,7 +194,7 @@ struct hfd_plan_s {
     void* dF = nullptr;         // their x-pass spectra [chunk][6][Lx/2 + 1][ny]
     double* dscale = nullptr;   // -1/(Lx Ly) per zeta of a chunk
     int dchunk = 0;
-    double* partial = nullptr;  // reduction partials [batch_max][ntiles][2 nz]
+    double* partial = nullptr;  // reduction partials [batch_max][2 nz][ntiles]
     int ntiles = 0;
     // equidistant stack: layer sum by FFT along z (path 4)
     bool eq3d = false;
@@ -767,6 +768,9 @@ hfd_status setup_derivatives(hfd_plan p, hipStream_t s)
     for (size_t k = 0; k < count.size(); ++k)
         for (int i = 0; i < count[k]; ++i) p->zeta_host[k * p->nzeta_max + i] = zeta[k * nmax + i];
     p->itab_host = itab;
+    p->ni_max = 0;
+    for (int g = 0; g < p->G; ++g)
+        p->ni_max = std::max(p->ni_max, itab[(size_t)g * p->itab_stride]);
     p->nzeta = count;
     p->dgroup = first;
     HFD_HIP(hipMemcpyAsync(p->zeta_dev, p->zeta_host.data(), sizeof(double) * p->zeta_host.size(),
@@ -1238,10 +1242,10 @@ hfd_status hfd_demag_vjp(hfd_plan p, const void* m, const void* grad_h, void* gr
     } else {
         // (the five-pass paths use Mh and Hh themselves: grad_m first)
         if (grad_m) HFD_TRY(run_field(p, grad_h, grad_m, batch, 1, s));
-        HFD_HIP(launch_xfwd(p->fp64, p->Lx, grad_h, p->X1, p->nx, p->ny, nsig, p->twx, s));
+        HFD_HIP(launch_xfwd(p->fp64, p->Lx, grad_h, p->X1, p->nx, p->ny, nsig, p->twx, s, xty_for(p, batch)));
         HFD_HIP(launch_yfwd(p->fp64, p->Ly, p->X1, p->Hh, p->ny, ncols, p->twy, s));
     }
-    HFD_HIP(launch_xfwd(p->fp64, p->Lx, m, p->X1, p->nx, p->ny, nsig, p->twx, s));
+    HFD_HIP(launch_xfwd(p->fp64, p->Lx, m, p->X1, p->nx, p->ny, nsig, p->twx, s, xty_for(p, batch)));
     HFD_HIP(launch_yfwd(p->fp64, p->Ly, p->X1, p->Mh, p->ny, ncols, p->twy, s));
     const int bpg = batch / p->G;
     const bool stored = (p->flags & HFD_STORE_DTENSOR) != 0;
@@ -1252,7 +1256,7 @@ hfd_status hfd_demag_vjp(hfd_plan p, const void* m, const void* grad_h, void* gr
     }
     if (stored) {
         HFD_HIP(launch_tgrad(p->fp64, p->Mh, p->Hh, p->nz, p->M, p->Ly, 0, batch, p->Q, p->qcs,
-                             p->qslot, p->D, p->nzeta_max, p->itab, p->itab_stride, p->lp, bpg, p->QX,
+                             p->qslot, p->D, p->nzeta_max, p->itab, p->itab_stride, p->ni_max, p->lp, bpg, p->QX,
                              p->QY, p->partial, s));
     } else {
         // recompute the derivative tensor of one group of stacks at a time
@@ -1261,7 +1265,7 @@ hfd_status hfd_demag_vjp(hfd_plan p, const void* m, const void* grad_h, void* gr
             HFD_TRY(compute_derivatives(p, (int)k, s));
             HFD_HIP(launch_tgrad(p->fp64, p->Mh, p->Hh, p->nz, p->M, p->Ly, g0 * bpg, (g1 - g0) * bpg,
                                  p->Q, p->qcs, p->qslot, p->D, p->nzeta_max, p->itab,
-                                 p->itab_stride, p->lp, bpg, p->QX, p->QY, p->partial, s));
+                                 p->itab_stride, p->ni_max, p->lp, bpg, p->QX, p->QY, p->partial, s));
         }
     }
     HFD_HIP(launch_tgrad_finish(p->partial, p->ntiles, batch, p->nz, p->itab, p->itab_stride, bpg,

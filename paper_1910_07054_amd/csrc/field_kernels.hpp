@@ -1022,7 +1022,7 @@ __global__ __launch_bounds__(NT) void k_mix_tile(const cpx<R>* Mh, cpx<R>* Hh, i
     const R sg = (!packed && p == 1 && t != 0) ? R(-1) : R(1);
     // a lane of the packed column reads row kx = 0 or kx = M (adjacent rows)
     const UniformBuf<R> qb(Q + (long long)tab_row(kx, M) * qcs,
-                           __builtin_amdgcn_readfirstlane((unsigned)((packed ? 2 : 1) * qcs * sizeof(R))));
+                           (unsigned)((packed ? 2 : 1) * qcs * sizeof(R)));
     const int gi = part * W + w, i0 = gi * IB;   // this wave's target group
     const bool pace = W > 8;
     int rowbase[IB];   // pair (i, j >= i) is rowbase + j

@@ -59,8 +59,19 @@ template <typename R>
 struct UniformBuf {
     __amdgpu_buffer_rsrc_t rsrc;
     __device__ __forceinline__ UniformBuf(const R* base, unsigned bytes)
-        : rsrc(__builtin_amdgcn_make_buffer_rsrc((void*)base, (short)0, (int)bytes, 0x00020000))
+        : rsrc(__builtin_amdgcn_make_buffer_rsrc((void*)uniform(base), (short)0,
+                                                 (int)__builtin_amdgcn_readfirstlane(bytes), 0x00020000))
     {
+    }
+    // The base and the size pinned to scalar registers: where the compiler forms
+    // either on the vector unit, a descriptor built from it counts as differing
+    // between lanes, and every load becomes a loop over its distinct values.
+    static __device__ __forceinline__ const R* uniform(const R* p)
+    {
+        const unsigned long long a = (unsigned long long)p;
+        const unsigned lo = __builtin_amdgcn_readfirstlane((unsigned)a);
+        const unsigned hi = __builtin_amdgcn_readfirstlane((unsigned)(a >> 32));
+        return (const R*)(((unsigned long long)hi << 32) | lo);
     }
     // element at (scalar element offset s) + (lane element offset v)
     __device__ __forceinline__ R ld(unsigned v, unsigned s) const

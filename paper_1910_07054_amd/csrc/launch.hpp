@@ -115,8 +115,10 @@ hipError_t launch_zdft3(bool out_fp64, const double* Q2, void* T3, int nz, int L
 hipError_t launch_eq3d_mix(bool fp64, int LZ, void* Mh, void* Bc, void* Hh, void* HBc, int nz, int M,
                            int LY, int B, const void* T3, int QY, const void* twz, hipStream_t s);
 
-// thickness-gradient reduction over the spectra (states b0 .. b0+nb-1, nb a
-// multiple of bpg); partial: [states][tgrad_tiles(M, LY)][2 nz]
+// thickness-gradient reduction over the spectra (ni_max: the largest position count
+// NI of the stacks; states b0 .. b0+nb-1, nb a
+// multiple of bpg); partial: [states][2 nz][tgrad_tiles(M, LY)]
+// (kx columns of 32 ky pairs each, and one for the self-mirrored points of kx = M)
 int tgrad_tiles(int M, int LY);
 // Per-geometry interface table of the thickness gradient (ints): [0] NI, the
 // number of interface positions; pinfo[nsp] at `info` (rank r*4 + 1 if the top
@@ -140,7 +142,7 @@ __host__ __device__ inline ITabLayout itab_layout(int nz)
 }
 hipError_t launch_tgrad(bool fp64, const void* Mh, const void* Gh, int nz, int M, int LY, int b0,
                         int nb, const void* Q, long long qcs, const int* qslot, const void* D, int nzt,
-                        const int* itab, int itab_stride, const void* lp, int bpg,
+                        const int* itab, int itab_stride, int ni_max, const void* lp, int bpg,
                         int QX, int QY, double* partial, hipStream_t s);
 hipError_t launch_tgrad_finish(const double* partial, int nparts, int B, int nz, const int* itab,
                                int itab_stride, int bpg, double* grad_t, hipStream_t s);

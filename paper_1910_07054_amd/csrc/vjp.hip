@@ -19,9 +19,17 @@
 //   P(p, q) = Re conj(Ghat_p) . D(z_p - z_q) Mhat_q,
 // D = dK/dzeta the normalized DFT of -1/(4 pi dx dy) dPsi/dz.  The 1/t_l
 // factor of Ghat adds -L_l / t_l to the top of layer l and +L_l / t_l to its
-// bottom, L_l = sum_j Re conj(G_l) . T^{lj} M_j the layer's share of L.  Each
-// D(z_p - z_q) is read once per frequency, where a sum over ordered layer pairs
-// and their four offsets reads it up to eight times.  The half spectrum holds
+// bottom, L_l = sum_j Re conj(G_l) . T^{lj} M_j the layer's share of L.
+// In the rotated components (X, sg Y, iZ) (sg = -1 for ky < 0) D(zeta) is a real
+// 3x3 matrix K per frequency and D(-zeta) is -K^T, so for z_p > z_q the pair's
+// contribution is one number,
+//   s = P(p, q) - P(q, p) = Ghat_p . (K Mhat_q) + Mhat_p . (K Ghat_q),
+// added to p and subtracted from q (dot products over real and imaginary
+// parts).  The stored tensor blocks S^{lj} = t_l T^{lj} are real in these components as
+// well and S^{jl} is the transpose: S M_j and S G_j of a pair l <= j give its part
+// of L_l and of L_j.  Each D and each S is read once per frequency, where a sum
+// over ordered layer pairs and their four offsets reads D up to eight times.
+// The half spectrum holds
 // kx in [1, M) once (weight 2, the mirror -kx is the complex conjugate) and
 // the packed column 0 carries kx = 0 and kx = Lx/2 (weight 1 each).
 // Position p has rank r_p (r = l for bot_l, l + 1 for top_l) and
@@ -42,21 +50,6 @@ __device__ inline double wave_sum(double v)
     return v;
 }
 
-template <typename T>
-__device__ inline T block_sum(T v, T* red)
-{
-    // wave reduction then across waves (blockDim.x multiple of 64, <= 1024)
-    for (int off = 32; off > 0; off >>= 1) v += __shfl_down(v, off, 64);
-    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-    __syncthreads();
-    if (lane == 0) red[w] = v;
-    __syncthreads();
-    T s = T(0);
-    if (threadIdx.x == 0)
-        for (int k = 0; k < (int)(blockDim.x >> 6); ++k) s += red[k];
-    return s;  // valid in thread 0
-}
-
 // Re conj(g) . A m for the symmetric block A with real xx, yy, zz, xy and
 // imaginary i xz, i yz entries; g, m = (re, im) x 3, arithmetic in double.
 template <typename T>
@@ -73,7 +66,347 @@ __device__ inline double gAm(const double g[6], double xx, double yy, double zz,
     return g[0] * vxr + g[1] * vxi + g[2] * vyr + g[3] * vyi + g[4] * vzr + g[5] * vzi;
 }
 
+// v = A m for a real block A = [[xx, xy, xz], [xy, yy, yz], [-xz, -yz, zz]] on the real and the
+// imaginary parts of m (re, im of the three components), then g . v
+__device__ __forceinline__ double dot_block(const double (&g)[6], double xx, double yy, double zz,
+                                            double xy, double xz, double yz, const double (&m)[6])
+{
+    double s = 0.0;
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+        const double X = m[h], Y = m[2 + h], Z = m[4 + h];
+        s = fma(g[h], fma(xz, Z, fma(xy, Y, xx * X)), s);
+        s = fma(g[2 + h], fma(yz, Z, fma(yy, Y, xy * X)), s);
+        s = fma(g[4 + h], fma(-xz, X, fma(-yz, Y, zz * Z)), s);
+    }
+    return s;
+}
+
 }  // namespace
+
+template <typename R>
+struct alignas(4 * sizeof(R)) MG {
+    cpx<R> m, g;
+};
+
+// One block per (state, kx, 32 lateral frequency pairs): lanes l and 32 + l of
+// every wave take ky = t and LY - t (t = 0: ky = 0 and LY/2), which share every
+// quadrant value of D and S; in the packed column lane p = 0 takes A(t) with row
+// kx = 0 and lane p = 1 B(t) with row kx = M; the self-mirrored points t = 0 take
+// A there, and B in an extra tile of their own.
+// The tile's M and G spectra (rotated; in the packed column as they are, A and B
+// are formed in FP64 where they are used) are staged in LDS and shared by the
+// block's 4 (or 2) waves, which take groups of QC source positions and of QC
+// layers in turn: a group's spectra stay in registers (FP64) while the wave
+// walks the positions above them, or the layers up to them, with the next one's
+// D or S entries in flight.  Each wave keeps its own per-position sums in LDS,
+// added up over waves and lanes at the end in a fixed order.
+// Block order: groups of 8 tiles, within a group every state of the launch,
+// with the 8 tiles on consecutive block indices: the states of one tile are 8
+// indices apart, so they run one after the other on one XCD and read that
+// tile's slice of the offset table D (shared by every stack when stored) and
+// of the tensor table through its L2.
+// Bound by FP64 arithmetic: per tile 5 k fused multiply-adds of the products and
+// 3.5 k conversions and sums.  16 states of 256 x 256 x 10: 1390 -> 1060 us (306 M
+// vector instructions, 0.7 ms of issue; 2.4 GB fetched instead of 6.9), one state
+// 64 x 64 x 3 in FP64 42 -> 16 us.  Groups of 2 take 1270 us (the conversions of the walked
+// position are shared by fewer products), of 4 as much as of 3 (two blocks of 4 waves
+// per CU either way).
+// itab per geometry: see itab_layout.  D per geometry: [QX][nzt][6][QY], nzt D slots per row.
+// lp per geometry: 1/t_l, then the trace term of the diagonal blocks.
+// partial[b][2nz][tile]: the tile's position gradients.
+template <typename R>
+__global__ __launch_bounds__(256, 2) void k_tgrad(
+    const cpx<R>* __restrict__ Mh, const cpx<R>* __restrict__ Gh, int nz, int M, int LY,
+    const R* __restrict__ Q, long long qcs, const int* __restrict__ qslot, const R* __restrict__ D, int nzt,
+    const int* __restrict__ itab, int itab_stride, const R* __restrict__ lp, int bpg, int QY, int b0, int nst,
+    int ntiles, double* __restrict__ partial)
+{
+    constexpr int QC = 3;
+    const int L = blockIdx.x, r8 = L >> 3;
+    const int tg = __builtin_amdgcn_readfirstlane(r8 / nst);
+    const int slot = tg * 8 + (L & 7);
+    if (slot >= ntiles) return;
+    // the last tile: the self-mirrored points of the packed column with row kx = M
+    const bool mirror = slot == ntiles - 1;
+    const int tile = mirror ? 0 : slot;
+    const int b = b0 + r8 - tg * nst;
+    const int geom = __builtin_amdgcn_readfirstlane(b / bpg);
+    const int half = LY >> 1, tpk = (half + 31) >> 5;
+    const int kx = __builtin_amdgcn_readfirstlane(tile / tpk), kyb = tile - kx * tpk;
+    const int lane = threadIdx.x & 63, W = blockDim.x >> 6;
+    const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int t0 = kyb * 32 + (lane & 31), p2 = lane >> 5;
+    const bool active = t0 < half;
+    const int t = active ? t0 : 0;
+    const int ky = p2 == 0 ? t : (t == 0 ? half : LY - t);
+    const int kq = p2 == 0 ? t : (t == 0 ? half : t);
+    const bool packed = kx == 0;
+    const R sg = (!packed && p2 == 1 && t != 0) ? R(-1) : R(1);
+    // half spectrum: kx and -kx; packed column: ky and -ky except the self-mirrored points
+    const double weight = !active || (mirror && t != 0) ? 0.0 : (packed && t == 0 ? 1.0 : 2.0);
+    const int S3 = 3 * nz;
+    const long long sst = (long long)M * LY;
+    const cpx<R>* mb = Mh + ((long long)b * S3 * M + kx) * LY + ky;
+    const cpx<R>* gb = Gh + ((long long)b * S3 * M + kx) * LY + ky;
+    const int* sl = qslot + (long long)geom * (nz * (nz + 1) / 2);  // the stack's pair slots
+    const R* lpg = lp + (long long)geom * 2 * nz;
+    const int* it = itab + (long long)geom * itab_stride;
+    const ITabLayout lay = itab_layout(nz);
+    const int NI = it[0];
+    const int* pinfo = it + lay.info;
+    const int* pbot = it + lay.pbot;
+    const int* ptop = it + lay.ptop;
+    const int* zpq = it + lay.zpq;
+    const long long drow = (long long)nzt * 6 * QY;
+    const int trow = tab_row(kx, M);
+    const UniformBuf<R> dbuf(D + (long long)trow * drow,
+                             (unsigned)((packed ? 2 : 1) * drow * sizeof(R)));
+    const UniformBuf<R> qbuf(Q + (long long)trow * qcs,
+                             (unsigned)((packed ? 2 : 1) * qcs * sizeof(R)));
+
+    extern __shared__ __align__(16) unsigned char smem_raw[];
+    double* accw = reinterpret_cast<double*>(smem_raw) + (size_t)w * NI * 64 + lane;  // [W][NI][64]
+    // (M, G) of component c, layer l: [nz][3][64]
+    MG<R>* sm = reinterpret_cast<MG<R>*>(smem_raw + sizeof(double) * 64 * (size_t)W * NI) + lane;
+    for (int v = 0; v < NI; ++v) accw[v * 64] = 0.0;
+
+    const bool rowM = packed && ((p2 == 1 && t != 0) || mirror);
+    const unsigned vd = (unsigned)(kq + (rowM ? drow : 0LL)), vq = (unsigned)(kq + (rowM ? qcs : 0LL));
+    // three layers per wave at a time, all 18 values requested together
+    for (int l0 = w * 3; l0 < nz; l0 += W * 3) {
+        cpx<R> zm[3][3], zg[3][3];
+#pragma unroll
+        for (int k = 0; k < 3; ++k)
+#pragma unroll
+            for (int c = 0; c < 3; ++c) {
+                const int s = c * nz + (l0 + k < nz ? l0 + k : nz - 1);
+                zm[k][c] = mb[s * sst];
+                zg[k][c] = gb[s * sst];
+            }
+#pragma unroll
+        for (int k = 0; k < 3; ++k)
+#pragma unroll
+            for (int c = 0; c < 3; ++c) {
+                cpx<R> vm = zm[k][c], vg = zg[k][c];
+                if (!packed) {
+                    if (c == 1) { vm = cscale(vm, sg); vg = cscale(vg, sg); }
+                    if (c == 2) { vm = {-vm.y, vm.x}; vg = {-vg.y, vg.x}; }
+                }
+                if (l0 + k < nz) sm[((l0 + k) * 3 + c) * 64] = {vm, vg};
+            }
+    }
+    __syncthreads();
+    auto sweep = [&](auto column) {
+        constexpr bool PACKED = decltype(column)::value;
+        // layer l's spectra
+        auto layer = [&](int l, double (&m)[6], double (&g)[6]) {
+#pragma unroll
+            for (int c = 0; c < 3; ++c) {
+                const MG<R> v = sm[(l * 3 + c) * 64];
+                m[2 * c] = v.m.x;
+                m[2 * c + 1] = v.m.y;
+                g[2 * c] = v.g.x;
+                g[2 * c + 1] = v.g.y;
+                if constexpr (PACKED) {
+                    // A(t) = (Z(t) + conj Z(-t)) / 2 on lane 0, B(t) = (Z(t) - conj Z(-t)) / (2i) on lane 1;
+                    // the self-mirrored points take A, then B
+                    const MG<R> o = sm[(l * 3 + c) * 64 + (p2 == 0 ? 32 : -32)];
+                    auto part = [&](cpx<R> z, cpx<R> n, double& x, double& y) {
+                        if (t == 0) {
+                            x = mirror ? z.y : z.x;
+                            y = 0.0;
+                        } else {
+                            const double re = p2 == 0 ? (double)z.x + n.x : (double)n.y + z.y;
+                            const double im = p2 == 0 ? (double)z.y - n.y : (double)z.x - n.x;
+                            x = 0.5 * re;
+                            y = 0.5 * im;
+                        }
+                        if (c == 2) {
+                            const double r = x;
+                            x = -y;
+                            y = r;
+                        }
+                    };
+                    part(v.m, o.m, m[2 * c], m[2 * c + 1]);
+                    part(v.g, o.g, g[2 * c], g[2 * c + 1]);
+                }
+            }
+        };
+        // position p: Mhat = -M (top of rk - 1) + M (bottom of rk) in plan precision,
+        // Ghat = G / t - G / t in FP64
+        auto position = [&](int p, double (&m)[6], double (&g)[6]) {
+            const int info = pinfo[p], rk = info >> 2;
+            const int la = (info & 1) ? rk - 1 : rk, lb = (info & 2) ? rk : rk - 1;
+            const R sa = (info & 1) ? R(-1) : R(0), sb = (info & 2) ? R(1) : R(0);
+            const double wa = -(double)sa * (double)lpg[la], wb = -(double)sb * (double)lpg[lb];
+            if constexpr (PACKED) {
+                double ma[6], ga[6];
+                layer(la, ma, ga);
+                layer(lb, m, g);
+#pragma unroll
+                for (int c = 0; c < 6; ++c) {
+                    m[c] = (R)((double)sa * ma[c] + (double)sb * m[c]);
+                    g[c] = wa * ga[c] + wb * g[c];
+                }
+            } else if ((info & 3) == 3) {
+#pragma unroll
+                for (int c = 0; c < 3; ++c) {
+                    const MG<R> x = sm[(la * 3 + c) * 64], y = sm[(lb * 3 + c) * 64];
+                    m[2 * c] = y.m.x - x.m.x;
+                    m[2 * c + 1] = y.m.y - x.m.y;
+                    g[2 * c] = fma(wa, (double)x.g.x, wb * (double)y.g.x);
+                    g[2 * c + 1] = fma(wa, (double)x.g.y, wb * (double)y.g.y);
+                }
+            } else {
+                const R sm1 = sa + sb;
+                const double w1 = (info & 1) ? wa : wb;
+#pragma unroll
+                for (int c = 0; c < 3; ++c) {
+                    const MG<R> x = sm[(la * 3 + c) * 64];
+                    m[2 * c] = sm1 * x.m.x;
+                    m[2 * c + 1] = sm1 * x.m.y;
+                    g[2 * c] = w1 * (double)x.g.x;
+                    g[2 * c + 1] = w1 * (double)x.g.y;
+                }
+            }
+        };
+        // groups u = 0, 1, .. of source positions from the lowest and of layers from the
+        // highest, both by falling cost, dealt to the waves in turn and back
+        const int ni = (NI + QC - 1) / QC, nl = (nz + QC - 1) / QC;
+        for (int r = 0; r * W < 2 * (ni > nl ? ni : nl); ++r) {
+            const int e = r * W + ((r & 1) ? W - 1 - w : w), u = e >> 1;
+            if ((e & 1) == 0) {
+                if (u >= ni) continue;
+                // source positions q0 .. q0 + QC - 1 against the positions above them
+                const int q0 = u * QC;
+                double mq[QC][6], gq[QC][6], aq[QC];
+#pragma unroll
+                for (int k = 0; k < QC; ++k) {
+                    position(q0 + k < NI ? q0 + k : NI - 1, mq[k], gq[k]);
+                    aq[k] = 0.0;
+                }
+                int sn[QC];   // table entries of the position to fetch next
+                auto slots = [&](int p) {
+#pragma unroll
+                    for (int k = 0; k < QC; ++k)
+                        sn[k] = zpq[(p < NI ? p : NI - 1) * lay.nsp + (q0 + k < NI ? q0 + k : NI - 1)];
+                };
+                auto fetch = [&](int p, R (&d)[QC][6]) {
+#pragma unroll
+                    for (int k = 0; k < QC; ++k)
+#pragma unroll
+                        for (int c = 0; c < 6; ++c) d[k][c] = dbuf.ld(vd, (unsigned)(((sn[k] >> 1) * 6 + c) * QY));
+                    slots(p + 1);
+                };
+                auto apply = [&](int p, const R (&d)[QC][6]) {
+                    double mp[6], gp[6], sp = 0.0;
+                    position(p, mp, gp);
+#pragma unroll
+                    for (int k = 0; k < QC; ++k)
+                        if (q0 + k < p) {
+                            const double xx = d[k][0], yy = d[k][1], zz = d[k][2], xy = d[k][3], xz = d[k][4],
+                                         yz = d[k][5];
+                            const double s = dot_block(gp, xx, yy, zz, xy, xz, yz, mq[k]) +
+                                             dot_block(mp, xx, yy, zz, xy, xz, yz, gq[k]);
+                            sp += s;
+                            aq[k] -= s;
+                        }
+                    accw[p * 64] += sp;
+                };
+                R d0[QC][6], d1[QC][6];
+                slots(q0 + 1);
+                fetch(q0 + 1, d0);
+                for (int p = q0 + 1; p < NI; p += 2) {
+                    fetch(p + 1, d1);
+                    apply(p, d0);
+                    if (p + 1 >= NI) break;
+                    fetch(p + 2, d0);
+                    apply(p + 1, d1);
+                }
+#pragma unroll
+                for (int k = 0; k < QC; ++k)
+                    if (q0 + k < NI) accw[(q0 + k) * 64] += aq[k];
+            } else {
+                if (u >= nl) continue;
+                // the 1/t_l factor: top_l gets -L_l / t_l, bot_l gets +L_l / t_l; layers j0 .. j0 + QC - 1
+                // against the layers up to them (the lowest group may reach below layer 0)
+                const int j0 = nz - (u + 1) * QC, jn = j0 + QC;
+                double mj[QC][6], gj[QC][6], aj[QC];
+#pragma unroll
+                for (int k = 0; k < QC; ++k) {
+                    layer(j0 + k > 0 ? j0 + k : 0, mj[k], gj[k]);
+                    if constexpr (PACKED)
+#pragma unroll
+                        for (int c = 0; c < 6; ++c) mj[k][c] = (R)mj[k][c];
+                    aj[k] = 0.0;
+                }
+                int sn[QC];   // slots of the layer to fetch next
+                auto slots = [&](int l) {
+#pragma unroll
+                    for (int k = 0; k < QC; ++k) {
+                        const int j = j0 + k > 0 ? j0 + k : 0, a = l < j ? l : j;
+                        sn[k] = sl[a * nz - a * (a - 1) / 2 + (j - a)];
+                    }
+                };
+                auto fetch = [&](int l, R (&d)[QC][5]) {
+#pragma unroll
+                    for (int k = 0; k < QC; ++k)
+#pragma unroll
+                        for (int c = 0; c < 5; ++c) d[k][c] = qbuf.ld(vq, (unsigned)((sn[k] * 5 + c) * QY));
+                    slots(l + 1);
+                };
+                auto add = [&](int l, double v) {
+                    const double f = (double)lpg[l] * (double)lpg[l] * v;
+                    accw[ptop[l] * 64] -= f;
+                    accw[pbot[l] * 64] += f;
+                };
+                auto apply = [&](int l, const R (&d)[QC][5]) {
+                    double ml[6], gl[6], x = 0.0;
+                    layer(l, ml, gl);
+                    if constexpr (PACKED)
+#pragma unroll
+                        for (int c = 0; c < 6; ++c) ml[c] = (R)ml[c];
+#pragma unroll
+                    for (int k = 0; k < QC; ++k) {
+                        const int j = j0 + k;
+                        if (j >= l) {
+                            const double xx = d[k][0], yy = d[k][1], xy = d[k][2], xz = d[k][3], yz = d[k][4];
+                            const double zz = -(xx + yy) + (l == j ? (double)lpg[nz + l] : 0.0);
+                            x += dot_block(gl, xx, yy, zz, xy, xz, yz, mj[k]);
+                            if (j > l) aj[k] += dot_block(ml, xx, yy, zz, xy, xz, yz, gj[k]);
+                        }
+                    }
+                    add(l, x);
+                };
+                R d0[QC][5], d1[QC][5];
+                slots(0);
+                fetch(0, d0);
+                for (int l = 0; l < jn; l += 2) {
+                    fetch(l + 1, d1);
+                    apply(l, d0);
+                    if (l + 1 >= jn) break;
+                    fetch(l + 2, d0);
+                    apply(l + 1, d1);
+                }
+#pragma unroll
+                for (int k = 0; k < QC; ++k)
+                    if (j0 + k >= 0) add(j0 + k, aj[k]);
+            }
+        }
+    };
+    if (packed) sweep(std::true_type{});
+    else sweep(std::false_type{});
+    __syncthreads();
+    double* out = partial + (long long)b * 2 * nz * ntiles + slot;
+    const double* acc0 = reinterpret_cast<const double*>(smem_raw) + lane;
+    for (int v = w; v < NI; v += W) {
+        double sv = 0.0;
+        for (int k = 0; k < W; ++k) sv += acc0[(size_t)(k * NI + v) * 64];
+        sv = wave_sum(sv * weight);
+        if (lane == 0) out[(long long)v * ntiles] = sv;
+    }
+}
 
 // QC (4 or 8) consecutive table entries from a 4 QC-byte aligned address
 template <int QC>
@@ -87,7 +420,8 @@ __device__ inline void load_chunk(const int* __restrict__ src, int (&dst)[QC])
     }
 }
 
-// Per-position gradient sums of one wave over its 64 frequencies of row kx
+// Stacks whose spectra do not fit in LDS: per-position gradient sums of one wave
+// over its 64 frequencies of row kx
 // (PACKED: the packed column, rows 0 and M from the unpacked pair A, B).
 // Sources (interface positions, then layers) are taken in chunks of QC held
 // in registers; for each target the loads of the next target are issued
@@ -307,17 +641,9 @@ __device__ inline void tgrad_row(const cpx<R>* __restrict__ mb, const cpx<R>* __
 // ky = t and LY - t (t = ty*32 + s; lane 2s+1 of t = 0 takes ky = LY/2), which
 // share every quadrant value of D and Q.  Each lane accumulates its own
 // per-position sums in LDS; the block sums them over the lanes at the end.
-// Block order: groups of 8 tiles, within a group every state of the launch,
-// with the 8 tiles on consecutive block indices: the states of one tile are 8
-// indices apart, so they run one after the other on one XCD and read that
-// tile's slice of the offset table D (shared by every stack when stored) and
-// of their geometry's Q through its L2, instead of streaming the whole table
-// once per state.
-// itab per geometry: see itab_layout.  D per geometry: [QX][nzt][6][QY], nzt D slots per row.
-// lp per geometry: 1/t_l, then the trace term of the diagonal blocks.
-// partial[b][tile][2nz]: the block's position gradients.
+// Block order and arguments as k_tgrad.
 template <typename R, int QC>
-__global__ __launch_bounds__(64) void k_tgrad(const cpx<R>* __restrict__ Mh,
+__global__ __launch_bounds__(64) void k_tgrad_rows(const cpx<R>* __restrict__ Mh,
                                               const cpx<R>* __restrict__ Gh, int nz, int M, int LY,
                                               const R* __restrict__ Q, long long qcs,
                                               const int* __restrict__ qslot,
@@ -360,31 +686,45 @@ __global__ __launch_bounds__(64) void k_tgrad(const cpx<R>* __restrict__ Mh,
         tgrad_row<R, QC, false>(mb, gb, sst, nz, M, kx, ky, kyn, kq, sgy, active ? 2.0 : 0.0, Q,
                                 qcs, sl, D, nzt, it, lpg, QY, acc);
     __syncthreads();
-    double* out = partial + ((long long)b * ntiles + tile) * NS;
+    double* out = partial + (long long)b * NS * (ntiles + 1) + tile;
     for (int v = 0; v < NI; ++v) {
         const double sv = wave_sum(acc[v * 64 + lane]);
-        if (lane == 0) out[v] = sv;
+        if (lane == 0) {
+            out[(long long)v * (ntiles + 1)] = sv;
+            // (k_tgrad's extra tile: its points are in tile 0 here)
+            if (tile == 0) out[(long long)v * (ntiles + 1) + ntiles] = 0.0;
+        }
     }
 }
 
 // Sum the tile partials of each position (fixed order) and apply the stacking
 // chain rule dL/dt_k = sum_p [k < r_p] dL/dz_p.
-__global__ __launch_bounds__(256) void k_tgrad_finish(const double* __restrict__ partial, int nparts,
-                                                      int nz, const int* __restrict__ itab,
-                                                      int itab_stride, int bpg,
-                                                      double* __restrict__ grad_t)
+__global__ __launch_bounds__(1024) void k_tgrad_finish(const double* __restrict__ partial, int nparts,
+                                                       int nz, const int* __restrict__ itab,
+                                                       int itab_stride, int bpg,
+                                                       double* __restrict__ grad_t)
 {
-    __shared__ double red[4];
     __shared__ double gp[128];
-    const int b = blockIdx.x;
+    const int b = blockIdx.x, lane = threadIdx.x & 63;
     const int* it = itab + (long long)(b / bpg) * itab_stride;
-    const int NI = it[0], NS = 2 * nz;
-    for (int v = 0; v < NI; ++v) {
-        double s = 0.0;
-        for (int k = threadIdx.x; k < nparts; k += blockDim.x)
-            s += partial[((long long)b * nparts + k) * NS + v];
-        s = block_sum(s, red);
-        if (threadIdx.x == 0) gp[v] = s;
+    const int NI = it[0];
+    // one wave per position, 16 partials per lane requested together (2048 tiles: 30 us
+    // with 4 on half the waves)
+    for (int v = threadIdx.x >> 6; v < NI; v += (int)(blockDim.x >> 6)) {
+        const double* src = partial + ((long long)b * 2 * nz + v) * nparts;
+        double t = 0.0;
+        for (int k0 = 0; k0 < nparts; k0 += 1024) {
+            double x[16];
+#pragma unroll
+            for (int e = 0; e < 16; ++e) {
+                const int k = k0 + 64 * e + lane;
+                x[e] = src[k < nparts ? k : nparts - 1];
+            }
+#pragma unroll
+            for (int e = 0; e < 16; ++e) t += k0 + 64 * e + lane < nparts ? x[e] : 0.0;
+        }
+        t = wave_sum(t);
+        if (lane == 0) gp[v] = t;
     }
     __syncthreads();
     for (int k = threadIdx.x; k < nz; k += blockDim.x) {
@@ -397,15 +737,48 @@ __global__ __launch_bounds__(256) void k_tgrad_finish(const double* __restrict__
 
 int tgrad_tiles(int M, int LY)
 {
-    return M * ((LY / 2 + 31) / 32);
+    return M * ((LY / 2 + 31) / 32) + 1;
+}
+
+// LDS of k_tgrad: the sums of its waves and the staged spectra of M and G
+template <typename R>
+static size_t tgrad_lds(int waves, int nz, int ni)
+{
+    return sizeof(double) * 64 * (size_t)waves * ni + sizeof(MG<R>) * 64 * 3 * (size_t)nz;
+}
+
+// 4 waves where they fit, else 2, else one wave per tile without staging (which
+// takes 3.2 and 3.5 times as long at 64 x 64 x 24 and 32 in FP32, 4.7 at 18 in FP64)
+template <typename R>
+static hipError_t tgrad_r(const void* Mh, const void* Gh, int nz, int M, int LY, int b0, int nb, const void* Q,
+                          long long qcs, const int* qslot, const void* D, int nzt, const int* itab,
+                          int itab_stride, int ni_max, const void* lp, int bpg, int QY, int ntiles, unsigned nblk,
+                          double* partial, hipStream_t s)
+{
+    constexpr size_t kMax = 163840;
+    const int waves = tgrad_lds<R>(4, nz, ni_max) <= kMax ? 4 : (tgrad_lds<R>(2, nz, ni_max) <= kMax ? 2 : 0);
+    if (waves > 0) {
+        const size_t lds = tgrad_lds<R>(waves, nz, ni_max);
+        const hipError_t e = ensure_lds_limit((const void*)k_tgrad<R>, lds > 65536 ? (int)kMax : 0);
+        if (e != hipSuccess) return e;
+        hipLaunchKernelGGL(k_tgrad<R>, dim3(nblk), dim3(64 * waves), lds, s, (const cpx<R>*)Mh,
+                           (const cpx<R>*)Gh, nz, M, LY, (const R*)Q, qcs, qslot, (const R*)D, nzt, itab,
+                           itab_stride, (const R*)lp, bpg, QY, b0, nb, ntiles, partial);
+    } else {
+        const size_t lds = sizeof(double) * 64 * (size_t)ni_max;
+        hipLaunchKernelGGL((k_tgrad_rows<R, 4>), dim3(nblk), dim3(64), lds, s, (const cpx<R>*)Mh,
+                           (const cpx<R>*)Gh, nz, M, LY, (const R*)Q, qcs, qslot, (const R*)D, nzt, itab,
+                           itab_stride, (const R*)lp, bpg, QY, b0, nb, ntiles - 1, partial);
+    }
+    return hipGetLastError();
 }
 
 hipError_t launch_tgrad(bool fp64, const void* Mh, const void* Gh, int nz, int M, int LY, int b0,
                         int nb, const void* Q, long long qcs, const int* qslot, const void* D, int nzt,
-                        const int* itab, int itab_stride, const void* lp, int bpg,
+                        const int* itab, int itab_stride, int ni_max, const void* lp, int bpg,
                         int QX, int QY, double* partial, hipStream_t s)
 {
-    if (nz < 1 || nz > 64 || nb < 1 || bpg < 1 || nb % bpg || LY < 2 || (LY & (LY - 1)))
+    if (nz < 1 || nz > 64 || ni_max < 1 || ni_max > 2 * nz || nb < 1 || bpg < 1 || nb % bpg || LY < 2 || (LY & (LY - 1)))
         return hipErrorInvalidValue;
     (void)QX;  // D and Q rows are addressed through nzt, qcs and QY
     // one row of D or Q is a buffer with 32-bit byte offsets
@@ -415,25 +788,17 @@ hipError_t launch_tgrad(bool fp64, const void* Mh, const void* Gh, int nz, int M
     const int ntiles = tgrad_tiles(M, LY);
     const long long nblk = (long long)((ntiles + 7) / 8) * 8 * nb;
     if (nblk > 0x7fffffffLL) return hipErrorInvalidValue;
-    const size_t lds = sizeof(double) * 64 * 2 * nz;  // >= NI x 64
-    if (fp64)
-        hipLaunchKernelGGL((k_tgrad<double, 4>), dim3((unsigned)nblk), dim3(64), lds, s,
-                           (const cpx<double>*)Mh, (const cpx<double>*)Gh, nz, M, LY,
-                           (const double*)Q, qcs, qslot, (const double*)D, nzt, itab, itab_stride,
-                           (const double*)lp, bpg, QY, b0, nb, ntiles, partial);
-    else
-        hipLaunchKernelGGL((k_tgrad<float, 4>), dim3((unsigned)nblk), dim3(64), lds, s,
-                           (const cpx<float>*)Mh, (const cpx<float>*)Gh, nz, M, LY,
-                           (const float*)Q, qcs, qslot, (const float*)D, nzt, itab, itab_stride,
-                           (const float*)lp, bpg, QY, b0, nb, ntiles, partial);
-    return hipGetLastError();
+    return fp64 ? tgrad_r<double>(Mh, Gh, nz, M, LY, b0, nb, Q, qcs, qslot, D, nzt, itab, itab_stride, ni_max,
+                                  lp, bpg, QY, ntiles, (unsigned)nblk, partial, s)
+                : tgrad_r<float>(Mh, Gh, nz, M, LY, b0, nb, Q, qcs, qslot, D, nzt, itab, itab_stride, ni_max,
+                                 lp, bpg, QY, ntiles, (unsigned)nblk, partial, s);
 }
 
 hipError_t launch_tgrad_finish(const double* partial, int nparts, int B, int nz, const int* itab,
                                int itab_stride, int bpg, double* grad_t, hipStream_t s)
 {
     if (nz < 1 || nz > 64 || B < 1 || bpg < 1) return hipErrorInvalidValue;
-    hipLaunchKernelGGL(k_tgrad_finish, dim3(B), dim3(256), 0, s, partial, nparts, nz, itab,
+    hipLaunchKernelGGL(k_tgrad_finish, dim3(B), dim3(1024), 0, s, partial, nparts, nz, itab,
                        itab_stride, bpg, grad_t);
     return hipGetLastError();
 }

@@ -195,3 +195,21 @@ def test_thickness_gradient_degenerate_lateral_shapes(nx, ny):
     ref = oracle.thickness_grad(nx, ny, 1.0, 2.0, zb, t, m[0], g[0])
     assert np.abs(gt[0] - ref).max() < 1e-10 * np.abs(ref).max(), (gt[0], ref)
     plan.destroy()
+
+
+@pytest.mark.parametrize("fp64", [False, True])
+@pytest.mark.parametrize("nz", [2, 3, 4, 16, 17, 22, 23])
+def test_thickness_gradient_group_and_staging_edges(nz, fp64):
+    """Layer counts around the groups of three positions and layers and around
+    the largest stacks whose spectra are staged in LDS (22 layers in FP32, 16 in
+    FP64); columns of more than one ky tile, touching layers and gaps mixed."""
+    wl = W.small_case(3, 34, nz, seed=430 + nz)
+    plan = plan_for(wl, flags=hfd.HFD_FP64 if fp64 else hfd.HFD_FP32)
+    g = np.random.default_rng(nz).standard_normal(wl.m.shape)
+    dt = np.float64 if fp64 else np.float32
+    _, gt = _vjp(plan, wl.m, g, want_m=False)
+    ref = oracle.thickness_grad(wl.nx, wl.ny, wl.dx, wl.dy, wl.z_bottom[0], wl.thickness[0],
+                                wl.m[0].astype(dt).astype(np.float64), g[0].astype(dt).astype(np.float64))
+    err = np.abs(gt[0] - ref).max() / np.abs(ref).max()
+    assert err < (1e-10 if fp64 else 2e-5), err
+    plan.destroy()
