@@ -199,7 +199,6 @@ struct hfd_plan_s {
     // equidistant stack: layer sum by FFT along z (path 4)
     bool eq3d = false;
     int Lz = 0;                 // padded length along z
-    void* Bc = nullptr;         // [2][batch_max][S][Ly]: split-off column Lx/2 in / out
     void* twz = nullptr;        // plan precision, length Lz
     // field path: 0 fused y-pass, 1 five-pass generic mixing, 2 five-pass batched
     // FP32 mixing, 3 five-pass split-BF16 MFMA mixing, 4 equidistant (z FFT);
@@ -311,7 +310,7 @@ void free_plan_memory(hfd_plan p)
     if (p->twx == p->twx64) p->twx = nullptr;  // FP64 plans share the FP64 tables
     if (p->twy == p->twy64) p->twy = nullptr;
     void* bufs[] = {p->Q, p->lp, p->twx, p->twy, p->twx64, p->twy64, p->X1, p->Mh, p->Hh,
-                    p->D, p->itab, p->zeta_dev, p->partial, p->dW, p->dF, p->dscale, p->Bc, p->twz,
+                    p->D, p->itab, p->zeta_dev, p->partial, p->dW, p->dF, p->dscale, p->twz,
                     p->sW, p->sF, p->spg, p->sscale, p->sQ2, p->qslot};
     for (void* b : bufs)
         if (b) (void)hipFree(b);
@@ -324,7 +323,7 @@ void free_plan_memory(hfd_plan p)
     p->itab = nullptr;
     p->zeta_dev = nullptr;
     p->partial = nullptr;
-    p->Bc = p->twz = nullptr;
+    p->twz = nullptr;
     p->sW = nullptr;
     p->sF = nullptr;
     p->spg = nullptr;
@@ -948,11 +947,8 @@ hfd_status run_field(hfd_plan p, const void* in, void* out, int batch, int adjoi
         mark();
         if (on()) {
             if (path == 4) {
-                // equidistant: unpack the packed column, z pass, repack
-                char* bc = (char*)p->Bc;
-                char* hbc = bc + (size_t)p->batch_max * 3 * p->nz * p->Ly * p->csz;
-                HFD_HIP(launch_eq3d_mix(p->fp64, p->Lz, p->Mh, bc, p->Hh, hbc, p->nz, p->M, p->Ly,
-                                        batch, p->Q, p->QY, p->twz, s));
+                HFD_HIP(launch_eq3d_mix(p->fp64, p->Lz, p->Mh, p->Hh, p->nz, p->M, p->Ly, batch, p->Q,
+                                        p->QY, p->twz, s));
             } else if (path == 2 || path == 3) {
                 // packed column by the generic kernel, the rest batched
                 HFD_HIP(launch_mix_generic(p->fp64, p->Mh, p->Hh, p->nz, p->M, p->Ly, batch, p->Q,
@@ -1045,7 +1041,6 @@ hfd_status hfd_setup_tensor(hfd_plan* out, int nx, int ny, double dx, double dy,
     const long long S = 3LL * nz;
     const long long q_per_geom = p->eq3d ? mul_ll(mul_ll((long long)(p->Lz / 2 + 1) * 6, p->QX), p->QY)
                                          : mul_ll(mul_ll((long long)p->P * 5, p->QX), p->QY);
-    const long long bc = p->eq3d ? mul_ll(mul_ll(2LL * batch_max, S), (long long)p->Ly * (long long)p->csz) : 0;
     const long long q_elems = mul_ll(q_per_geom, n_geom);
     const long long x1 = mul_ll(mul_ll(mul_ll((long long)batch_max, S), p->M), (long long)ny * (long long)p->csz);
     const long long mh = mul_ll(mul_ll(mul_ll((long long)batch_max, S), p->M), (long long)p->Ly * (long long)p->csz);
@@ -1071,7 +1066,7 @@ hfd_status hfd_setup_tensor(hfd_plan* out, int nx, int ny, double dx, double dy,
     if (st) { delete p; return st; }
     size_t freeb = 0, totalb = 0;
     if (hipMemGetInfo(&freeb, &totalb) == hipSuccess) {
-        const long double need = (long double)q_elems * p->rsz + (long double)x1 + 2.0L * mh + (long double)bc;
+        const long double need = (long double)q_elems * p->rsz + (long double)x1 + 2.0L * mh;
         if (need > (long double)freeb) {
             delete p;
             return fail(HFD_ENOMEM, "plan needs " + std::to_string((double)need) + " bytes of device memory, " +
@@ -1093,10 +1088,6 @@ hfd_status hfd_setup_tensor(hfd_plan* out, int nx, int ny, double dx, double dy,
         if (st) break;
         st = dev_alloc(&p->Hh, p->mh_bytes, "spectrum workspace");
         if (st) break;
-        if (p->eq3d) {
-            st = dev_alloc(&p->Bc, (size_t)bc, "split-column workspace");
-            if (st) break;
-        }
         st = upload_twiddles(p, s);
         if (st) break;
         st = alloc_setup_scratch(p);
@@ -1490,7 +1481,6 @@ hfd_status hfd_get_info(hfd_plan p, hfd_info* info)
     info->fused = p->fused; info->fp64 = p->fp64; info->mix_bf16 = p->bf16;
     info->tensor_bytes = p->q_geom_stride * (long long)p->G * (long long)p->rsz;
     info->work_bytes = (long long)(p->x1_bytes + 2 * p->mh_bytes);
-    if (p->eq3d) info->work_bytes += 2LL * p->batch_max * 3 * p->nz * p->Ly * (long long)p->csz;
     info->equidistant = p->eq3d;
     info->Lz = p->Lz;
     info->tensor_slots = p->eq3d ? 0 : p->nslot_used;

@@ -47,139 +47,123 @@ __global__ __launch_bounds__(256) void k_zdft3(const double* __restrict__ Q2, R*
     T3[idx] = (R)(acc / (double)LZ);
 }
 
-// The packed column 0 of every signal holds Z = A + iB with A, B the y-spectra
-// of the real columns kx = 0 and kx = Lx/2.  Unpack: A into column 0, B into
-// Bc[sig][ky]; one thread per ky pair (t, LY - t).
-template <typename R>
-__global__ __launch_bounds__(256) void k_unpack0(cpx<R>* __restrict__ Mh, cpx<R>* __restrict__ Bc,
-                                                 int M, int LY, long long nsig)
-{
-    const int HP = LY / 2 + 1;
-    const long long idx = (long long)blockIdx.x * blockDim.x + threadIdx.x;
-    if (idx >= nsig * HP) return;
-    const long long sig = idx / HP;
-    const int t = (int)(idx % HP), tm = (LY - t) & (LY - 1);
-    cpx<R>* col = Mh + sig * M * LY;
-    cpx<R>* bc = Bc + sig * LY;
-    const cpx<R> z1 = col[t], z2 = col[tm];
-    const cpx<R> a = {R(0.5) * (z1.x + z2.x), R(0.5) * (z1.y - z2.y)};
-    const cpx<R> b = {R(0.5) * (z1.y + z2.y), R(0.5) * (z2.x - z1.x)};
-    col[t] = a;
-    bc[t] = b;
-    if (tm != t) {
-        col[tm] = cconj(a);
-        bc[tm] = cconj(b);
-    }
-}
-
-// Repack after the z pass: column 0 = HA + i HB.
-template <typename R>
-__global__ __launch_bounds__(256) void k_repack0(cpx<R>* __restrict__ Hh, const cpx<R>* __restrict__ HBc,
-                                                 int M, int LY, long long nsig)
-{
-    const long long idx = (long long)blockIdx.x * blockDim.x + threadIdx.x;
-    if (idx >= nsig * LY) return;
-    const long long sig = idx / LY;
-    const int ky = (int)(idx % LY);
-    cpx<R>* col = Hh + sig * M * LY;
-    const cpx<R> a = col[ky], b = HBc[sig * LY + ky];
-    col[ky] = {a.x - b.y, a.y + b.x};
-}
-
+// A wave takes NQ transforms of one component, lane = g NQ + q with q the
+// transform (consecutive ky) and g the lane's place in it: a load or store
+// moves NQ consecutive ky of each of the GT layers.  16 values per lane from 64
+// points on, so that NQ = 16 ky are one 128-byte line (8 at 128 points).
 template <typename R, int LZ>
 struct ZPassShape {
-    static constexpr int V = fft_vals(LZ), GT = LZ / V;
-    static constexpr int NT = 256, NG = NT / GT;
-    // ky points per block: the tile holds 3 transforms of LZ values per point
-    static constexpr int TP = (sizeof(cpx<R>) * 3 * 16 * fft_region(LZ) <= 49152) ? 16 : 8;
+    static constexpr int V = LZ <= 32 ? fft_vals(LZ) : 16;
+    static constexpr int GT = LZ / V, NQ = 64 / GT;
+    static constexpr int PB = NQ >= 16 ? 1 : 16 / NQ;   // waves per component
+    static constexpr int TP = NQ * PB;                  // ky points per block
+    static constexpr int NT = 3 * 64 * PB;
+    // LDS slots per transform: odd, so that lanes on consecutive ky take
+    // different banks
+    static constexpr int RS = fft_region(LZ) | 1;
+    static constexpr int LZH = LZ / 2 + 1;
 };
 
-// z pass: block = TP consecutive ky of one kx column (kx = M is the split-off
-// column Lx/2) of one state.  The 3 nz spectra of the tile are staged in LDS
-// zero padded to LZ along the layer axis, transformed along z, multiplied by
-// the real symmetric 3x3 tensor, transformed back, and the first nz layers
-// written out.
+// z pass: block = TP consecutive ky of one kx column of one state.  The 3 nz
+// spectra go from memory into the first radix pass of their transforms along z
+// (zero padded to LZ), are multiplied by the real symmetric 3x3 tensor, a thread
+// taking kz and LZ - kz, which share its entries, and leave from the last pass of
+// the inverse transforms, first nz layers only.
+// Column 0 holds Z = A + iB, A and B the y spectra of the real columns kx = 0 and
+// kx = Lx/2: its blocks run A(ky) = (Z(ky) + conj Z(-ky)) / 2 and then
+// B(ky) = (Z(ky) - conj Z(-ky)) / (2i) through the same steps and store A' + iB'.
+// Bound by the Infinity Cache and HBM: 256 x 256 x 32 (101 MB each way, 52 MB of tensor
+// read twice) 115 -> 72 us with the unpacking and repacking of column 0 (two launches
+// before), 256 x 256 x 16 in FP64 86 -> 58.  Staging the zero-padded spectra in LDS with
+// 8 lanes per transform on consecutive layers moved 64-byte pieces and kept the
+// product's lanes on one LDS bank.  Registers for 3 waves per SIMD: 4 spill the 64-point
+// transform in FP32 (72 -> 158 us).
 template <typename R, int LZ>
-__global__ __launch_bounds__(256) void k_zpass3(const cpx<R>* __restrict__ Mh, const cpx<R>* __restrict__ Bc,
-                                                cpx<R>* __restrict__ Hh, cpx<R>* __restrict__ HBc, int nz,
-                                                int M, int LY, const R* __restrict__ T3, int QY,
-                                                const cpx<R>* __restrict__ twz)
+__global__ __launch_bounds__((ZPassShape<R, LZ>::NT), (sizeof(R) == 4 ? 3 : 2)) void k_zpass3(
+    const cpx<R>* __restrict__ Mh, cpx<R>* __restrict__ Hh, int nz, int M, int LY, const R* __restrict__ T3,
+    int QY, const cpx<R>* __restrict__ twz)
 {
     using SH = ZPassShape<R, LZ>;
-    constexpr int TP = SH::TP, GT = SH::GT, NG = SH::NG, NT = SH::NT, LZH = LZ / 2 + 1;
-    constexpr int LZP = fft_region(LZ);  // LDS slots per transform
-    __shared__ cpx<R> sh[3 * TP * LZP];
-    const int kx = blockIdx.y, b = blockIdx.z;
-    const int ky0 = blockIdx.x * TP;
-    const int S = 3 * nz;
-    const int tid = threadIdx.x, grp = tid / GT, g = tid % GT;
-    const bool split = kx == M;
-    const long long sstride = split ? (long long)LY : (long long)M * LY;
-    const cpx<R>* src = split ? Bc : Mh + (long long)kx * LY;
-    cpx<R>* dst = split ? HBc : Hh + (long long)kx * LY;
-    Twiddles<R, LZ> tw;
+    constexpr int TP = SH::TP, NT = SH::NT, RS = SH::RS, LZH = SH::LZH, V = SH::V, NQ = SH::NQ;
+    __shared__ cpx<R> sh[3 * TP * RS];
+    const int kx = blockIdx.y, b = blockIdx.z, ky0 = blockIdx.x * TP;
+    const int tid = threadIdx.x, w = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
+    const int c = w / SH::PB, pt = (w % SH::PB) * NQ + lane % NQ, g = lane / NQ;
+    const int tr = c * TP + pt, ky = ky0 + pt;
+    const bool live = ky < LY;
+    const long long sst = (long long)M * LY;
+    const long long base = ((long long)b * 3 * nz + c * nz) * sst + (long long)kx * LY;
+    const cpx<R>* src = Mh + base + (live ? ky : 0);
+    const cpx<R>* srn = Mh + base + (live ? (LY - ky) & (LY - 1) : 0);
+    cpx<R>* dst = Hh + base + ky;
+    cpx<R>* reg = sh + tr * RS;
+    Twiddles<R, LZ, V> tw;
     tw.load(g, twz, 1);
 
-    // stage: sh[(p * 3 + c) * LZP + l], zero for l >= nz
-    for (int idx = tid; idx < TP * 3 * LZ; idx += NT) {
-        const int p = idx % TP, r = idx / TP, c = r / LZ, l = r - c * LZ;
-        const int ky = ky0 + p;
-        cpx<R> v = {R(0), R(0)};
-        if (l < nz && ky < LY) v = src[((long long)b * S + c * nz + l) * sstride + ky];
-        sh[(p * 3 + c) * LZP + l] = v;
-    }
-    __syncthreads();
-    for (int tr = grp; tr < 3 * TP; tr += NG) {
-        cpx<R>* reg = sh + tr * LZP;
-        wave_fft<R, LZ, false>(reg, g, tw, [&](int pos) -> cpx<R> { return reg[pos]; },
-                               [&](int pos, cpx<R> v) { reg[pos] = v; });
-    }
-    __syncthreads();
-    // 3x3 product per (point, kz)
-    const R* Tk = T3 + (long long)kx * LZH * 6 * QY;
-    for (int idx = tid; idx < TP * LZ; idx += NT) {
-        const int p = idx % TP, kz = idx / TP;
-        const int ky = ky0 + p;
-        if (ky >= LY) continue;
-        const int kyq = ky <= LY / 2 ? ky : LY - ky;
-        const int kzq = kz <= LZ / 2 ? kz : LZ - kz;
-        const R sy = ky <= LY / 2 ? R(1) : R(-1);
-        const R sz = kz <= LZ / 2 ? R(1) : R(-1);
-        const R* t = Tk + (long long)kzq * 6 * QY + kyq;
-        const R xx = t[0], yy = t[QY], zz = t[2 * QY], xy = sy * t[3 * QY], xz = sz * t[4 * QY],
-                yz = sy * sz * t[5 * QY];
-        cpx<R>* v = sh + p * 3 * LZP + kz;
-        const cpx<R> X = v[0], Y = v[LZP], Z = v[2 * LZP];
-        v[0] = {xx * X.x + xy * Y.x + xz * Z.x, xx * X.y + xy * Y.y + xz * Z.y};
-        v[LZP] = {xy * X.x + yy * Y.x + yz * Z.x, xy * X.y + yy * Y.y + yz * Z.y};
-        v[2 * LZP] = {xz * X.x + yz * Y.x + zz * Z.x, xz * X.y + yz * Y.y + zz * Z.y};
-    }
-    __syncthreads();
-    for (int tr = grp; tr < 3 * TP; tr += NG) {
-        cpx<R>* reg = sh + tr * LZP;
-        wave_fft<R, LZ, true>(reg, g, tw, [&](int pos) -> cpx<R> { return reg[pos]; },
-                              [&](int pos, cpx<R> v) { reg[pos] = v; });
-    }
-    __syncthreads();
-    for (int idx = tid; idx < TP * 3 * nz; idx += NT) {
-        const int p = idx % TP, cl = idx / TP, c = cl / nz, l = cl - c * nz;
-        const int ky = ky0 + p;
-        if (ky < LY) dst[((long long)b * S + cl) * sstride + ky] = sh[(p * 3 + c) * LZP + l];
+    cpx<R> keep[V / 2 > 0 ? V / 2 : 1];  // A' of the packed column
+    for (int part = 0; part < (kx == 0 ? 2 : 1); ++part) {
+        cpx<R> v[V];
+        if (kx != 0) {
+            fft_first_loads<R, LZ, true>(v, g, [&](int l) -> cpx<R> {
+                return l < nz ? src[l * sst] : cpx<R>{R(0), R(0)};
+            });
+        } else {
+            fft_first_loads<R, LZ, true>(v, g, [&](int l) -> cpx<R> {
+                if (l >= nz) return {R(0), R(0)};
+                const cpx<R> z = src[l * sst], n = srn[l * sst];
+                return part == 0 ? cpx<R>{R(0.5) * (z.x + n.x), R(0.5) * (z.y - n.y)}
+                                 : cpx<R>{R(0.5) * (z.y + n.y), R(0.5) * (n.x - z.x)};
+            });
+            if (part > 0) __syncthreads();
+        }
+        wave_fft_pre<R, LZ, false, true>(reg, g, tw, v, [&](int pos, cpx<R> z) { reg[pos] = z; });
+        __syncthreads();
+        // 3x3 product per (point, +-kz)
+        const R* Tk = T3 + (long long)(part == 0 ? kx : M) * LZH * 6 * QY;
+        for (int idx = tid; idx < TP * LZH; idx += NT) {
+            const int p = idx % TP, kz = idx / TP, k1 = ky0 + p;
+            if (k1 >= LY) continue;
+            const R sy = k1 <= LY / 2 ? R(1) : R(-1);
+            const R* t = Tk + (long long)kz * 6 * QY + (k1 <= LY / 2 ? k1 : LY - k1);
+            const R xx = t[0], yy = t[QY], zz = t[2 * QY], xy = sy * t[3 * QY];
+            R xz = t[4 * QY], yz = sy * t[5 * QY];
+#pragma unroll
+            for (int h = 0; h < 2; ++h) {
+                if (h == 1 && (kz == 0 || 2 * kz == LZ)) break;
+                cpx<R>* w = sh + p * RS + (h == 0 ? kz : LZ - kz);
+                const cpx<R> X = w[0], Y = w[TP * RS], Z = w[2 * TP * RS];
+                w[0] = {xx * X.x + xy * Y.x + xz * Z.x, xx * X.y + xy * Y.y + xz * Z.y};
+                w[TP * RS] = {xy * X.x + yy * Y.x + yz * Z.x, xy * X.y + yy * Y.y + yz * Z.y};
+                w[2 * TP * RS] = {xz * X.x + yz * Y.x + zz * Z.x, xz * X.y + yz * Y.y + zz * Z.y};
+                xz = -xz;  // odd in kz
+                yz = -yz;
+            }
+        }
+        __syncthreads();
+        int i = 0;
+        wave_fft<R, LZ, true, false, true>(
+            reg, g, tw, [&](int pos) -> cpx<R> { return reg[pos]; },
+            [&](int l, cpx<R> z) {
+                cpx<R>& k = keep[i++];
+                if (kx == 0) z = part == 0 ? z : cpx<R>{k.x - z.y, k.y + z.x};
+                k = z;
+                if (live && l < nz && (kx != 0 || part == 1)) dst[l * sst] = z;
+            });
     }
 }
 
 namespace {
 
 template <typename R>
-hipError_t zpass_r(int LZ, const void* Mh, const void* Bc, void* Hh, void* HBc, int nz, int M,
-                   int LY, int B, const void* T3, int QY, const void* twz, hipStream_t s)
+hipError_t zpass_r(int LZ, const void* Mh, void* Hh, int nz, int M, int LY, int B, const void* T3, int QY,
+                   const void* twz, hipStream_t s)
 {
 #define HFD_ZPASS_CASE(L)                                                                          \
     case L: {                                                                                      \
-        dim3 grid((LY + ZPassShape<R, L>::TP - 1) / ZPassShape<R, L>::TP, M + 1, B);               \
-        hipLaunchKernelGGL((k_zpass3<R, L>), grid, dim3(256), 0, s, (const cpx<R>*)Mh,             \
-                           (const cpx<R>*)Bc, (cpx<R>*)Hh, (cpx<R>*)HBc, nz, M, LY, (const R*)T3,  \
-                           QY, (const cpx<R>*)twz);                                                \
+        dim3 grid((LY + ZPassShape<R, L>::TP - 1) / ZPassShape<R, L>::TP, M, B);                   \
+        hipLaunchKernelGGL((k_zpass3<R, L>), grid, dim3(ZPassShape<R, L>::NT), 0, s,               \
+                           (const cpx<R>*)Mh, (cpx<R>*)Hh, nz, M, LY, (const R*)T3, QY,            \
+                           (const cpx<R>*)twz);                                                    \
         return hipGetLastError();                                                                  \
     }
     switch (LZ) {
@@ -212,30 +196,12 @@ hipError_t launch_zdft3(bool out_fp64, const double* Q2, void* T3, int nz, int L
     return hipGetLastError();
 }
 
-hipError_t launch_eq3d_mix(bool fp64, int LZ, void* Mh, void* Bc, void* Hh, void* HBc, int nz, int M,
-                           int LY, int B, const void* T3, int QY, const void* twz, hipStream_t s)
+hipError_t launch_eq3d_mix(bool fp64, int LZ, const void* Mh, void* Hh, int nz, int M, int LY, int B,
+                           const void* T3, int QY, const void* twz, hipStream_t s)
 {
-    if (!Mh || !Bc || !Hh || !HBc || !T3 || !twz) return hipErrorInvalidValue;
-    const long long nsig = (long long)B * 3 * nz;
-    const long long n1 = nsig * (LY / 2 + 1), n2 = nsig * LY;
-    if ((n2 + 255) / 256 > 0x7fffffffLL) return hipErrorInvalidValue;
-    hipError_t e;
-    if (fp64) {
-        hipLaunchKernelGGL(k_unpack0<double>, dim3((unsigned)((n1 + 255) / 256)), dim3(256), 0, s,
-                           (cpx<double>*)Mh, (cpx<double>*)Bc, M, LY, nsig);
-        if ((e = hipGetLastError()) != hipSuccess) return e;
-        if ((e = zpass_r<double>(LZ, Mh, Bc, Hh, HBc, nz, M, LY, B, T3, QY, twz, s)) != hipSuccess) return e;
-        hipLaunchKernelGGL(k_repack0<double>, dim3((unsigned)((n2 + 255) / 256)), dim3(256), 0, s,
-                           (cpx<double>*)Hh, (const cpx<double>*)HBc, M, LY, nsig);
-    } else {
-        hipLaunchKernelGGL(k_unpack0<float>, dim3((unsigned)((n1 + 255) / 256)), dim3(256), 0, s,
-                           (cpx<float>*)Mh, (cpx<float>*)Bc, M, LY, nsig);
-        if ((e = hipGetLastError()) != hipSuccess) return e;
-        if ((e = zpass_r<float>(LZ, Mh, Bc, Hh, HBc, nz, M, LY, B, T3, QY, twz, s)) != hipSuccess) return e;
-        hipLaunchKernelGGL(k_repack0<float>, dim3((unsigned)((n2 + 255) / 256)), dim3(256), 0, s,
-                           (cpx<float>*)Hh, (const cpx<float>*)HBc, M, LY, nsig);
-    }
-    return hipGetLastError();
+    if (!Mh || !Hh || Mh == Hh || !T3 || !twz || B > 65535 || 2 * nz > (LZ < 2 ? 0 : LZ)) return hipErrorInvalidValue;
+    if (fp64) return zpass_r<double>(LZ, Mh, Hh, nz, M, LY, B, T3, QY, twz, s);
+    return zpass_r<float>(LZ, Mh, Hh, nz, M, LY, B, T3, QY, twz, s);
 }
 
 }  // namespace hfd

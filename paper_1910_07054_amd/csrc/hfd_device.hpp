@@ -259,9 +259,8 @@ struct TwCount<L, V, L> {
     static constexpr int value = 0;
 };
 
-template <typename R, int L>
+template <typename R, int L, int V = fft_vals(L)>
 struct Twiddles {
-    static constexpr int V = fft_vals(L);
     static constexpr int GT = L / V;
     static constexpr int N = TwCount<L, V>::value > 0 ? TwCount<L, V>::value : 1;
     cpx<R> w[N];
@@ -371,10 +370,10 @@ __device__ __forceinline__ void fft_pass(cpx<R> (&v)[V], cpx<R>* sh, int g, cons
 // The values a lane reads in the first pass, in register order, so that the
 // input of several transforms can be requested before any of them starts
 // (HIN: the zero upper half is not requested).
-template <typename R, int L, bool HIN = false, class Load>
-__device__ __forceinline__ void fft_first_loads(cpx<R> (&v)[fft_vals(L)], int g, Load load)
+template <typename R, int L, bool HIN = false, int V, class Load>
+__device__ __forceinline__ void fft_first_loads(cpx<R> (&v)[V], int g, Load load)
 {
-    constexpr int V = fft_vals(L), GT = L / V;
+    constexpr int GT = L / V;
     using P = PassShape<L, V, 1>;
     constexpr int STRIDE = L / P::RAD;
 #pragma unroll
@@ -387,22 +386,20 @@ __device__ __forceinline__ void fft_first_loads(cpx<R> (&v)[fft_vals(L)], int g,
 
 // One transform whose first-pass values are already in v (fft_first_loads).
 // sh: the group's LDS region of fft_region(L) values.
-template <typename R, int L, bool INV, bool HIN = false, bool HOUT = false, class Store>
-__device__ __forceinline__ void wave_fft_pre(cpx<R>* sh, int g, const Twiddles<R, L>& tw,
-                                             cpx<R> (&v)[fft_vals(L)], Store store)
+template <typename R, int L, bool INV, bool HIN = false, bool HOUT = false, int V, class Store>
+__device__ __forceinline__ void wave_fft_pre(cpx<R>* sh, int g, const Twiddles<R, L, V>& tw,
+                                             cpx<R> (&v)[V], Store store)
 {
-    constexpr int V = fft_vals(L);
     static_assert(L / V <= 64, "one transform must fit in a wavefront");
     auto none = [](int) { return cpx<R>{R(0), R(0)}; };
     fft_pass<R, L, V, INV, 1, 0, true, HIN, HOUT>(v, sh, g, tw.w, none, store);
 }
 
 // One transform with preloaded twiddles.
-template <typename R, int L, bool INV, bool HIN = false, bool HOUT = false, class Load, class Store>
-__device__ __forceinline__ void wave_fft(cpx<R>* sh, int g, const Twiddles<R, L>& tw, Load load,
+template <typename R, int L, bool INV, bool HIN = false, bool HOUT = false, int V, class Load, class Store>
+__device__ __forceinline__ void wave_fft(cpx<R>* sh, int g, const Twiddles<R, L, V>& tw, Load load,
                                          Store store)
 {
-    constexpr int V = fft_vals(L);
     static_assert(L / V <= 64, "one transform must fit in a wavefront");
     cpx<R> v[V];
     fft_pass<R, L, V, INV, 1, 0, false, HIN, HOUT>(v, sh, g, tw.w, load, store);

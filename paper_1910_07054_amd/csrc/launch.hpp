@@ -108,12 +108,11 @@ hipError_t launch_mix_batched(bool mfma, const void* Mh, void* Hh, int nz, int M
                               int bpg, int adjoint, hipStream_t s);
 
 // equidistant stacks: 3-D Fourier tensor from the per-offset 2D spectra, and
-// the z pass on the five-pass spectra (packed column unpacked into Bc and
-// repacked; Bc, HBc: [B][3nz][LY])
+// the z pass on the five-pass spectra (Hh != Mh)
 hipError_t launch_zdft3(bool out_fp64, const double* Q2, void* T3, int nz, int LZ, int QX, int QY,
                         hipStream_t s);
-hipError_t launch_eq3d_mix(bool fp64, int LZ, void* Mh, void* Bc, void* Hh, void* HBc, int nz, int M,
-                           int LY, int B, const void* T3, int QY, const void* twz, hipStream_t s);
+hipError_t launch_eq3d_mix(bool fp64, int LZ, const void* Mh, void* Hh, int nz, int M, int LY, int B,
+                           const void* T3, int QY, const void* twz, hipStream_t s);
 
 // thickness-gradient reduction over the spectra (ni_max: the largest position count
 // NI of the stacks; states b0 .. b0+nb-1, nb a

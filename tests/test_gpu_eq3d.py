@@ -47,6 +47,26 @@ def test_equidistant_field_matches_bruteforce(case, fp64):
     plan.destroy()
 
 
+# z pass: rows shorter than a block's ky points (Ly = 2, 4, 8), rows of several
+# blocks, layer counts that fill the padded length's half or are one short or
+# over, and Lx = 2, whose only columns are the two packed ones
+Z_EDGES = [(5, 1, 7), (6, 2, 16), (3, 4, 64), (1, 5, 17), (2, 40, 31), (9, 33, 4), (1, 3, 32), (4, 17, 63)]
+
+
+@pytest.mark.parametrize("fp64", [False, True], ids=["fp32", "fp64"])
+@pytest.mark.parametrize("case", Z_EDGES, ids=lambda c: "x".join(map(str, c)))
+def test_z_pass_at_block_and_layer_edges(case, fp64):
+    nx, ny, nz = case
+    rng = np.random.default_rng(950 + nz)
+    m = np.stack([W.random_unit(rng, (nz, ny, nx)) for _ in range(3)])
+    plan, zb = _plan(nx, ny, nz, 0.6, 0.75, fp64, 3)
+    h, mused = run_field(plan, m)
+    for b in range(3):
+        ref = oracle.field(nx, ny, DX, DY, zb, np.full(nz, 0.6), mused[b])
+        assert rel_err(h[b], ref) < (1e-10 if fp64 else 1e-5), b
+    plan.destroy()
+
+
 def test_equidistant_tensor_matches_oracle_transform():
     nx, ny, nz, t, pitch = 11, 7, 6, 0.9, 1.3
     plan, _ = _plan(nx, ny, nz, t, pitch, True, 1)
