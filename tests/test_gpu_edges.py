@@ -67,3 +67,22 @@ def test_rejected_batch_sizes():
     assert lib.hfd_demag_field(plan.handle, m.data_ptr(), h.data_ptr(), 2, None) == hfd.HFD_OK
     torch.cuda.synchronize()
     plan.destroy()
+
+
+# five-pass y transforms whose groups walk over several columns, a few blocks of
+# which have one round more than the others, and a call with few columns (the
+# five-pass path is forced where the fused one would be taken); Ly = 8, 64, 2048, 64
+@pytest.mark.parametrize("fp64", [False, True], ids=["fp32", "fp64"])
+@pytest.mark.parametrize("nx,ny,nz,B", [(128, 3, 7, 100), (40, 20, 6, 29), (5, 520, 2, 86), (130, 17, 1, 1)])
+def test_y_transforms_of_many_columns_match_bruteforce(nx, ny, nz, B, fp64):
+    wl = W.small_case(nx, ny, nz, seed=1500 + nz, batch=1)
+    one = wl.m[0]
+    m = np.stack([np.roll(one, 5 * b, axis=-1) for b in range(B)])
+    plan = hfd.Plan(nx, ny, wl.dx, wl.dy, wl.thickness[0], wl.z_bottom[0], batch_max=B,
+                    flags=hfd.HFD_FP64 if fp64 else hfd.HFD_FP32)
+    plan.set_path(B, 1, 0)
+    h, mused = run_field(plan, m)
+    for b in (0, B // 2, B - 1):
+        ref = oracle.field(nx, ny, wl.dx, wl.dy, wl.z_bottom[0], wl.thickness[0], mused[b])
+        assert rel_err(h[b], ref) < (1e-10 if fp64 else 1e-5), b
+    plan.destroy()
