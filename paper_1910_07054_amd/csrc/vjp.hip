@@ -96,7 +96,7 @@ struct alignas(4 * sizeof(R)) MG {
 // A there, and B in an extra tile of their own.
 // The tile's M and G spectra (rotated; in the packed column as they are, A and B
 // are formed in FP64 where they are used) are staged in LDS and shared by the
-// block's 4 (or 2) waves, which take groups of QC source positions and of QC
+// block's waves (1, 2 or 4), which take groups of QC source positions and of QC
 // layers in turn: a group's spectra stay in registers (FP64) while the wave
 // walks the positions above them, or the layers up to them, with the next one's
 // D or S entries in flight.  Each wave keeps its own per-position sums in LDS,
@@ -747,8 +747,21 @@ static size_t tgrad_lds(int waves, int nz, int ni)
     return sizeof(double) * 64 * (size_t)waves * ni + sizeof(MG<R>) * 64 * 3 * (size_t)nz;
 }
 
-// 4 waves where they fit, else 2, else one wave per tile without staging (which
-// takes 3.2 and 3.5 times as long at 64 x 64 x 24 and 32 in FP32, 4.7 at 18 in FP64)
+// Waves per tile: 4 where they fit, else 2, else one wave per tile without staging
+// (which takes 3.2 and 3.5 times as long at 64 x 64 x 24 and 32 in FP32, 4.7 at 18 in FP64).
+// Up to 4 layers have too few groups of positions and layers for 4 waves, up to 8
+// too few where blocks queue up anyway: whole calls with 1, 2 and 4 waves take
+//   250 x 250 x 2, 16 stacks 267, 304, 448 us     60 x 60 x 2, 1 stack 29, 26, 25
+//   128 x 128 x 4, 4 stacks   76,  64,  72        128 x 128 x 4, 1 stack 49, 38, 41
+//   250 x 250 x 5, 16 stacks 878, 919, 1049       128 x 128 x 5, 1 stack 81, 59, 54
+//   200 x 200 x 8, 16 stacks 1672 (2), 1755 (4)   256 x 256 x 9, 2 stacks 218 (2), 209 (4)
+//   256 x 256 x 10, 16 stacks 1777 (2), 1580 (4)
+static int tgrad_waves(int nz, unsigned nblk)
+{
+    if (nblk >= 4096) return nz <= 2 ? 1 : nz <= 8 ? 2 : 4;
+    return nz <= 4 && nblk >= 512 ? 2 : 4;
+}
+
 template <typename R>
 static hipError_t tgrad_r(const void* Mh, const void* Gh, int nz, int M, int LY, int b0, int nb, const void* Q,
                           long long qcs, const int* qslot, const void* D, int nzt, const int* itab,
@@ -756,7 +769,8 @@ static hipError_t tgrad_r(const void* Mh, const void* Gh, int nz, int M, int LY,
                           double* partial, hipStream_t s)
 {
     constexpr size_t kMax = 163840;
-    const int waves = tgrad_lds<R>(4, nz, ni_max) <= kMax ? 4 : (tgrad_lds<R>(2, nz, ni_max) <= kMax ? 2 : 0);
+    int waves = tgrad_waves(nz, nblk);
+    if (tgrad_lds<R>(waves, nz, ni_max) > kMax) waves = tgrad_lds<R>(2, nz, ni_max) <= kMax ? 2 : 0;
     if (waves > 0) {
         const size_t lds = tgrad_lds<R>(waves, nz, ni_max);
         const hipError_t e = ensure_lds_limit((const void*)k_tgrad<R>, lds > 65536 ? (int)kMax : 0);

@@ -213,3 +213,23 @@ def test_thickness_gradient_group_and_staging_edges(nz, fp64):
     err = np.abs(gt[0] - ref).max() / np.abs(ref).max()
     assert err < (1e-10 if fp64 else 2e-5), err
     plan.destroy()
+
+
+@pytest.mark.parametrize("fp64", [False, True])
+@pytest.mark.parametrize("nz,B", [(1, 60), (2, 60), (3, 60), (8, 60), (9, 60), (4, 8), (5, 8)])
+def test_thickness_gradient_waves_per_tile(nz, B, fp64):
+    """Both sides of each line of the waves-per-tile rule: 72 blocks per state,
+    so 4320 of them, or 576."""
+    wl = W.small_case(33, 3, nz, seed=460 + nz)
+    plan = hfd.Plan(wl.nx, wl.ny, wl.dx, wl.dy, wl.thickness[0], wl.z_bottom[0], batch_max=B,
+                    flags=hfd.HFD_FP64 if fp64 else hfd.HFD_FP32)
+    m = np.stack([np.roll(wl.m[0], b, axis=-1) for b in range(B)])
+    g = np.random.default_rng(nz).standard_normal(m.shape)
+    dt = np.float64 if fp64 else np.float32
+    _, gt = _vjp(plan, m, g, want_m=False)
+    for b in (0, B // 2, B - 1):
+        ref = oracle.thickness_grad(wl.nx, wl.ny, wl.dx, wl.dy, wl.z_bottom[0], wl.thickness[0],
+                                    m[b].astype(dt).astype(np.float64), g[b].astype(dt).astype(np.float64))
+        err = np.abs(gt[b] - ref).max() / np.abs(ref).max()
+        assert err < (1e-10 if fp64 else 2e-5), (b, err)
+    plan.destroy()
