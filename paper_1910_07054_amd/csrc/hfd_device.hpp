@@ -153,10 +153,55 @@ __device__ __forceinline__ void dft8(cpx<R>* v)
     v[7] = csub(e3, o3);
 }
 
+// 16 = 4 x 4: DFT4 of x[b], x[4 + b], x[8 + b], x[12 + b], factors w16^(b k), DFT4 over b.
+// The first step is left to `four`, which may know that its last two inputs are zero.
+template <typename R, bool INV, class Four>
+__device__ __forceinline__ void dft16(cpx<R>* v, Four four)
+{
+    const R c = R(0.70710678118654752440084436210484903928);
+    const R c1 = R(0.92387953251128675612818318939678828682);  // cos(pi/8)
+    const R s1 = R(0.38268343236508977172845998403039886676);  // sin(pi/8)
+    cpx<R> y[4][4];  // [b][k]
+#pragma unroll
+    for (int b = 0; b < 4; ++b) four(v[b], v[4 + b], v[8 + b], v[12 + b], y[b]);
+    const R d = INV ? R(-1) : R(1);
+    // z exp(-+ i phi), (x, y) = (cos, sin) phi
+    auto rot = [&](cpx<R> z, R x, R y) -> cpx<R> {
+        y *= d;
+        return {z.x * x + z.y * y, z.y * x - z.x * y};
+    };
+    auto eighth = [&](cpx<R> z) -> cpx<R> {  // exp(-+ i pi/4)
+        return INV ? cpx<R>{c * (z.x - z.y), c * (z.x + z.y)} : cpx<R>{c * (z.x + z.y), c * (z.y - z.x)};
+    };
+    y[1][1] = rot(y[1][1], c1, s1);
+    y[1][2] = eighth(y[1][2]);
+    y[1][3] = rot(y[1][3], s1, c1);
+    y[2][1] = eighth(y[2][1]);
+    y[2][2] = mul_mi<R, INV>(y[2][2]);
+    y[2][3] = mul_mi<R, INV>(eighth(y[2][3]));
+    y[3][1] = rot(y[3][1], s1, c1);
+    y[3][2] = mul_mi<R, INV>(eighth(y[3][2]));
+    y[3][3] = rot(y[3][3], -c1, -s1);
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+        dft4<R, INV>(y[0][k], y[1][k], y[2][k], y[3][k]);
+#pragma unroll
+        for (int q = 0; q < 4; ++q) v[k + 4 * q] = y[q][k];
+    }
+}
+
 template <typename R, int RAD, bool INV>
 __device__ __forceinline__ void dft(cpx<R>* v)
 {
-    if constexpr (RAD == 8) dft8<R, INV>(v);
+    if constexpr (RAD == 16) {
+        dft16<R, INV>(v, [](cpx<R> a, cpx<R> b, cpx<R> c, cpx<R> d, cpx<R> (&y)[4]) {
+            dft4<R, INV>(a, b, c, d);
+            y[0] = a;
+            y[1] = b;
+            y[2] = c;
+            y[3] = d;
+        });
+    } else if constexpr (RAD == 8) dft8<R, INV>(v);
     else if constexpr (RAD == 4) dft4<R, INV>(v[0], v[1], v[2], v[3]);
     else dft2<R, INV>(v);
 }
@@ -176,7 +221,11 @@ __device__ __forceinline__ void dft_half_in(cpx<R>* v)
         b1 = cadd(a0, t);
         b3 = csub(a0, t);
     };
-    if constexpr (RAD == 8) {
+    if constexpr (RAD == 16) {
+        dft16<R, INV>(v, [&](cpx<R> a, cpx<R> b, cpx<R>, cpx<R>, cpx<R> (&y)[4]) {
+            dft4h(a, b, y[0], y[1], y[2], y[3]);
+        });
+    } else if constexpr (RAD == 8) {
         const R c = R(0.70710678118654752440084436210484903928);
         cpx<R> e0, e1, e2, e3, o0, o1, o2, o3;
         dft4h(v[0], v[2], e0, e1, e2, e3);
@@ -211,18 +260,18 @@ __device__ __forceinline__ void dft_half_in(cpx<R>* v)
 // finished points writes pos = 8 j + r (first pass, lane j) or pos = 64 q + 8 r + k
 // (NS = 8, j = 8 q + k), the next one reads consecutive positions.  The exchange after
 // each pass has a layout of its own, slot(pos) = pos + (pos >> SHIFT) MULT:
-//   8-byte values, NS = 1: pos + pos/16 (writes 8 (j & 1) + j / 2 mod 16, reads aligned runs)
+//   8-byte values, NS = 1: pos + pos/16 (writes 8 (j & 1) + j / 2 mod 16, or j; reads aligned runs)
 //   8-byte values, NS = 8: pos + 8 (pos/64) (writes k + 8 q mod 16)
 //   NS > 8: as they are (both sides are runs of at least 16)
-//   16-byte values: pos + pos/8 (writes 9 j and k mod 8).
+//   16-byte values: pos + pos/8 (writes 9 j and k mod 8), pos + pos/16 after a first pass of radix 16.
 // With pos + pos/8 for both sizes the reads of 8-byte values took twice as long.
 // A lane's positions differ by constants that do not carry into pos >> SHIFT, so
 // their slots differ by compile-time constants and cost no address arithmetic.
 // A transform of length L uses fft_region(L) slots.
-template <typename R, int NS>
+template <typename R, int NS, int RAD>
 struct Exchange {
     static constexpr bool WIDE = sizeof(R) == 8;
-    static constexpr int SHIFT = WIDE ? 3 : (NS == 1 ? 4 : 6);
+    static constexpr int SHIFT = NS == 1 && RAD == 16 ? 4 : WIDE ? 3 : (NS == 1 ? 4 : 6);
     static constexpr int MULT = WIDE ? 1 : (NS == 1 ? 1 : (NS == 8 ? 8 : 0));
     __host__ __device__ static constexpr int slot(int pos) { return pos + (pos >> SHIFT) * MULT; }
 };
@@ -241,7 +290,15 @@ __host__ __device__ constexpr int fft_region(int L) { return L + (L >> 3); }
 template <int L, int V, int NS>
 struct PassShape {
     static constexpr int REM = L / NS;
-    static constexpr int RAD = (REM >= 8 && V % 8 == 0) ? 8 : ((REM >= 4 && V % 4 == 0) ? 4 : 2);
+    // radix 16 where it takes a pass less than 8 alone (128 = 16 8, 256 = 16 16,
+    // 1024 = 16 8 8, 2048 = 16 16 8; not 4096, whose twiddles then spill more in FP64).
+    // Each pass less is one exchange through LDS and one round of factors less, and the
+    // kept factors take fewer registers: 64 states of 512 x 512 x 4 fused 2038 -> 1804 us,
+    // 8 of 400 x 400 x 2 157 -> 102, 1024 x 1024 x 3 all transforms 175 -> 160, 128-point z
+    // pass of 4 states of 128 x 64 x 40 123 -> 109.  16 values per lane for 128 and 256
+    // points, where they are not there anyway, gain nothing.
+    static constexpr bool R16 = V % 16 == 0 && (REM == 16 || REM == 128 || REM == 256 || REM == 1024 || REM == 2048);
+    static constexpr int RAD = R16 ? 16 : (REM >= 8 && V % 8 == 0) ? 8 : ((REM >= 4 && V % 4 == 0) ? 4 : 2);
     static constexpr int NB = V / RAD;
     static constexpr bool LAST = (NS * RAD == L);
     static constexpr int NEXT = LAST ? L : NS * RAD;
@@ -292,9 +349,9 @@ struct Twiddles {
 // first pass neither loads nor transforms them.  HOUT: only the output
 // positions 0 .. L/2-1 are wanted (cropped result): the last pass stores only
 // those, and what feeds nothing else is not computed.
-// PREV: the finished points of the pass before the last one (layout of its exchange).
+// XIn: layout of the values the pass before wrote.
 template <typename R, int L, int V, bool INV, int NS, int OFF, bool PRE = false, bool HIN = false,
-          bool HOUT = false, int PREV = 1, class Load, class Store>
+          bool HOUT = false, class XIn = Exchange<R, 1, 8>, class Load, class Store>
 __device__ __forceinline__ void fft_pass(cpx<R> (&v)[V], cpx<R>* sh, int g, const cpx<R>* w,
                                          Load& load, Store& store)
 {
@@ -306,8 +363,7 @@ __device__ __forceinline__ void fft_pass(cpx<R> (&v)[V], cpx<R>* sh, int g, cons
     constexpr bool LAST = P::LAST;
     constexpr bool HALF_IN = FIRST && HIN;
     static_assert(L % (NS * RAD) == 0, "radix schedule");
-    using XIn = Exchange<R, PREV>;
-    using XOut = Exchange<R, NS>;
+    using XOut = Exchange<R, NS, RAD>;
     static_assert(FIRST || STRIDE % 8 == 0, "later passes read at multiples of 8");
     static_assert(LAST || RAD >= 8, "exchange layouts are for passes of radix 8 and 16");
 #pragma unroll
@@ -363,7 +419,7 @@ __device__ __forceinline__ void fft_pass(cpx<R> (&v)[V], cpx<R>* sh, int g, cons
     if constexpr (!LAST) {
         wave_sync();
         constexpr int here = NS > 1 ? NB * (RAD - 1) : 0;
-        fft_pass<R, L, V, INV, P::NEXT, OFF + here, false, false, HOUT, NS>(v, sh, g, w, load, store);
+        fft_pass<R, L, V, INV, P::NEXT, OFF + here, false, false, HOUT, XOut>(v, sh, g, w, load, store);
     }
 }
 

@@ -86,3 +86,19 @@ def test_y_transforms_of_many_columns_match_bruteforce(nx, ny, nz, B, fp64):
         ref = oracle.field(nx, ny, wl.dx, wl.dy, wl.z_bottom[0], wl.thickness[0], mused[b])
         assert rel_err(h[b], ref) < (1e-10 if fp64 else 1e-5), b
     plan.destroy()
+
+
+# transforms with radix-16 passes at 1024 and 2048 points: x passes (2000 cells: 2048
+# after the split), fused and five-pass y passes, the crop inside and at the end of
+# the half that the last pass stores
+@pytest.mark.parametrize("fp64", [False, True], ids=["fp32", "fp64"])
+@pytest.mark.parametrize("nx,ny,nz", [(513, 2, 2), (1024, 1, 1), (1100, 2, 1), (2, 257, 1), (3, 512, 4),
+                                      (2, 300, 5), (2, 513, 3), (1, 1024, 1)])
+def test_radix_16_transforms_match_bruteforce(nx, ny, nz, fp64):
+    wl = W.small_case(nx, ny, nz, seed=1600 + nx + ny, batch=2)
+    plan = plan_for(wl, flags=hfd.HFD_FP64 if fp64 else hfd.HFD_FP32)
+    h, mused = run_field(plan, wl.m)
+    for b in range(2):
+        ref = oracle.field(nx, ny, wl.dx, wl.dy, wl.z_bottom[0], wl.thickness[0], mused[b])
+        assert rel_err(h[b], ref) < (1e-10 if fp64 else 1e-5), b
+    plan.destroy()
