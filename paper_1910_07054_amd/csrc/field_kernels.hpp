@@ -519,11 +519,18 @@ struct MirrorPoints {
     }
 };
 
-template <int LY>
+// Threads of a fused block: at least one per frequency (and a wave), at most as many
+// as run the column's 3 nz transforms in one round (8 values each), within 512 below
+// 1024 points.
+template <int LY, int NZMAX>
 struct FusedShape {
-    // one thread per frequency from 512-point columns on; shorter columns
-    // get 512 threads too, so that more of their transforms run at once
-    static constexpr int NT = LY < 512 ? 512 : LY;
+    static constexpr int least = LY < 64 ? 64 : LY;
+    static constexpr int most()
+    {
+        int n = least;
+        while (n < 512 && n < 3 * NZMAX * LY / 8) n *= 2;
+        return n;
+    }
 };
 
 // ---------------------------------------------------------------------------
@@ -693,15 +700,15 @@ __device__ __forceinline__ void ymix_column(int kx, int b, int geom, cpx<R>* __r
 // Grid (M, states per stack, stacks): the stack index is blockIdx.z, so no
 // integer division is needed (on gfx950 it runs on the vector unit, and a
 // buffer descriptor built from its result is treated as a per-lane value).
-template <typename R, int LY, int NZMAX, bool ADJ>
-__global__ __launch_bounds__(FusedShape<LY>::NT) void k_ymix_fused(
+template <typename R, int LY, int NZMAX, bool ADJ, int NT>
+__global__ __launch_bounds__(NT) void k_ymix_fused(
     cpx<R>* __restrict__ X, int ny, int nz, int M, const R* __restrict__ Q, long long qcs,
     const int* __restrict__ qslot, int QY, const R* __restrict__ lp, int bpg,
     const cpx<R>* __restrict__ twy)
 {
     const int geom = blockIdx.z;
-    ymix_column<R, LY, NZMAX, ADJ, FusedShape<LY>::NT>(blockIdx.x, geom * bpg + blockIdx.y, geom, X, ny, nz, M, Q, qcs,
-                                   qslot, QY, lp, twy);
+    ymix_column<R, LY, NZMAX, ADJ, NT>(blockIdx.x, geom * bpg + blockIdx.y, geom, X, ny, nz, M, Q, qcs, qslot, QY, lp,
+                                       twy);
 }
 
 // ---------------------------------------------------------------------------

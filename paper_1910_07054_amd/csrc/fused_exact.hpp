@@ -17,7 +17,7 @@ hipError_t fused_exact_n(void* X, int ny, int M, int bpg, int G, const void* Q, 
         hipError_t e = ensure_lds_limit((const void*)k_ymix_fused_nz<float, LY, NZ, ADJ, NT>, 163840);
         if (e != hipSuccess) return e;
         if constexpr (!own_col0) {
-            e = ensure_lds_limit((const void*)k_ymix_fused<float, LY, 4, ADJ>, 163840);
+            e = ensure_lds_limit((const void*)k_ymix_fused<float, LY, 4, ADJ, LY>, 163840);
             if (e != hipSuccess) return e;
         }
     }
@@ -27,7 +27,7 @@ hipError_t fused_exact_n(void* X, int ny, int M, int bpg, int G, const void* Q, 
     if constexpr (!own_col0) {
         // the packed column 0 (kx = 0 and Lx/2) by the generic kernel
         static_assert(NZ <= 4, "generic 1024-point column kernel holds up to 4 layers");
-        hipLaunchKernelGGL((k_ymix_fused<float, LY, 4, ADJ>), dim3(1, bpg, G), dim3(FusedShape<LY>::NT),
+        hipLaunchKernelGGL((k_ymix_fused<float, LY, 4, ADJ, LY>), dim3(1, bpg, G), dim3(LY),
                            lds, s, (cpx<float>*)X, ny, NZ, M, (const float*)Q, qcs, qslot, QY,
                            (const float*)lp, bpg, (const cpx<float>*)tw);
     }

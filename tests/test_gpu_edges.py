@@ -102,3 +102,20 @@ def test_radix_16_transforms_match_bruteforce(nx, ny, nz, fp64):
         ref = oracle.field(nx, ny, wl.dx, wl.dy, wl.z_bottom[0], wl.thickness[0], mused[b])
         assert rel_err(h[b], ref) < (1e-10 if fp64 else 1e-5), b
     plan.destroy()
+
+
+# threads per block of the generic fused kernel: launches on both sides of the line
+# between one round of transforms and one thread per frequency, where the two differ
+@pytest.mark.parametrize("fp64", [False, True], ids=["fp32", "fp64"])
+@pytest.mark.parametrize("nx,ny,nz,B", [(33, 30, 3, 15), (33, 30, 3, 17), (33, 10, 8, 40), (33, 6, 12, 40),
+                                        (9, 60, 11, 33), (70, 100, 2, 3), (33, 3, 4, 3)])
+def test_fused_threads_per_block_match_bruteforce(nx, ny, nz, B, fp64):
+    wl = W.small_case(nx, ny, nz, seed=1700 + ny, batch=1)
+    m = np.stack([np.roll(wl.m[0], b, axis=-1) for b in range(B)])
+    plan = hfd.Plan(nx, ny, wl.dx, wl.dy, wl.thickness[0], wl.z_bottom[0], batch_max=B,
+                    flags=hfd.HFD_FP64 if fp64 else hfd.HFD_FP32)
+    h, mused = run_field(plan, m)
+    for b in (0, B // 2, B - 1):
+        ref = oracle.field(nx, ny, wl.dx, wl.dy, wl.z_bottom[0], wl.thickness[0], mused[b])
+        assert rel_err(h[b], ref) < (1e-10 if fp64 else 1e-5), b
+    plan.destroy()
