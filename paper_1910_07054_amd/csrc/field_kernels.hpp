@@ -24,16 +24,26 @@
 
 namespace hfd {
 
+// Values per lane of the x passes' transforms.  16 for 256 points (rows of 129 to 256
+// cells): two radix-16 passes with one exchange instead of 8 8 4 with two, and half
+// the threads per row, 16 states of 256 x 256 x 10 118 + 100 -> 91 + 82 us, 256 x 256 x 8
+// 8.1 + 7.3 -> 6.6 + 6.5, in FP64 9.9 + 10.0 -> 9.1 + 8.2.  For 128 points it pays with many
+// rows only (8 states of 100 x 60 x 12 9.7 + 8.3 -> 8.2 + 7.4, one of 128 x 128 x 8 3.5 + 3.3 ->
+// 3.9 + 3.6).  Forward passes whose spectra feed the thickness gradient keep 8 there
+// (XV below): it is an FP64 result of FP32 spectra, and another order of their
+// roundings moves its seventh digit.
+__host__ __device__ constexpr int x_vals(int M) { return M == 256 ? 16 : fft_vals(M); }
+
 // Rows are numbered flat over all signals (row r = signal r / ny, y = r % ny)
 // and a block takes TY consecutive rows, one wave or part of a wave per row,
 // RPG rows one after the other where TY rows would need more than 512 threads.
 // The transposed side of a pass moves TY consecutive y of one kx: TY = 16 rows
 // (8 in FP64) are one 128-byte line.  TYO = 0 picks that, or one wave of rows
 // if that is more, halved until the tile fits in 80 KB of LDS.
-template <typename R, int LX, int TYO = 0>
+template <typename R, int LX, int TYO = 0, int XV = x_vals(LX / 2)>
 struct XPassShape {
     static constexpr int M = LX / 2;
-    static constexpr int V = fft_vals(M);
+    static constexpr int V = XV;
     static constexpr int GT = M / V;
     // odd LDS row stride: the transposed accesses take 16 rows of one kx from
     // 16 different slots
@@ -125,12 +135,12 @@ __device__ __forceinline__ void real_split_inv(cpx<R>& a, cpx<R>& b, cpx<R> w, b
 // 4.2 TB/s; a copy runs at 4.9), those of one 256 x 256 x 8 state 9.1 + 8.7,
 // now 6.8 + 6.2.
 // ---------------------------------------------------------------------------
-template <typename R, int LX, int TYO = 0>
-__global__ __launch_bounds__((XPassShape<R, LX, TYO>::NT), (XPassShape<R, LX, TYO>::WPE)) void k_xfwd(
+template <typename R, int LX, int TYO = 0, int XV = x_vals(LX / 2)>
+__global__ __launch_bounds__((XPassShape<R, LX, TYO, XV>::NT), (XPassShape<R, LX, TYO, XV>::WPE)) void k_xfwd(
     const R* __restrict__ in, cpx<R>* __restrict__ out, int nx, int ny, int nrows, FastDiv dny,
     const cpx<R>* __restrict__ twx)
 {
-    using S = XPassShape<R, LX, TYO>;
+    using S = XPassShape<R, LX, TYO, XV>;
     constexpr int M = S::M, V = S::V, GT = S::GT, NG = S::NG, TY = S::TY, RS = S::RS, RPG = S::RPG;
     constexpr int KI = S::KI, KS = S::KS;
     extern __shared__ __align__(16) unsigned char smem_raw[];
@@ -159,7 +169,7 @@ __global__ __launch_bounds__((XPassShape<R, LX, TYO>::NT), (XPassShape<R, LX, TY
             });
         }
     }
-    Twiddles<R, M> tw;
+    Twiddles<R, M, S::V> tw;
     tw.load(g, twx, 2);
     const int rb = tid % TY, kb = tid / TY;
     cpx<R> ws[KI];
@@ -229,7 +239,7 @@ __global__ __launch_bounds__((XPassShape<R, LX, TYO>::NT), (XPassShape<R, LX, TY
         }
     }
     // (in FP64 the twiddles would not fit beside the pairs)
-    Twiddles<R, M> tw;
+    Twiddles<R, M, S::V> tw;
     if constexpr (sizeof(R) == 4) tw.load(g, twx, 2);
     __syncthreads();
     if constexpr (sizeof(R) == 8) tw.load(g, twx, 2);
@@ -266,18 +276,21 @@ __global__ __launch_bounds__((XPassShape<R, LX, TYO>::NT), (XPassShape<R, LX, TY
 // rows kx = 0 and LX/2 of x-odd components are exactly zero).
 // ---------------------------------------------------------------------------
 template <int LX, int TYO = 0>
-__global__ __launch_bounds__((XPassShape<double, LX, TYO>::NT), (XPassShape<double, LX, TYO>::WPE)) void k_xtab(
+using XTabShape = XPassShape<double, LX, TYO, fft_vals(LX / 2)>;
+
+template <int LX, int TYO = 0>
+__global__ __launch_bounds__((XTabShape<LX, TYO>::NT), (XTabShape<LX, TYO>::WPE)) void k_xtab(
     const double* __restrict__ in, double* __restrict__ out, int nx, int ny, int nrows,
     const cpx<double>* __restrict__ twx)
 {
     using R = double;
-    using S = XPassShape<R, LX, TYO>;
+    using S = XTabShape<LX, TYO>;
     constexpr int M = S::M, GT = S::GT, NG = S::NG, TY = S::TY, RS = S::RS;
     extern __shared__ __align__(16) unsigned char smem_raw[];
     cpx<R>* sh = reinterpret_cast<cpx<R>*>(smem_raw);
     const int r0 = blockIdx.x * TY;
     const int tid = threadIdx.x, grp = tid / GT, g = tid % GT;
-    Twiddles<R, M> tw;
+    Twiddles<R, M, S::V> tw;
     tw.load(g, twx, 2);
     for (int r = grp; r < TY; r += NG) {
         const int fr = r0 + r;

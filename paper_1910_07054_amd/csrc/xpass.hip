@@ -16,19 +16,19 @@ constexpr bool x_tile_ok()
     return S::GT * TY <= 1024 && S::GT * TY >= 64 && S::LDS <= 163840;
 }
 
-template <bool FWD, typename R, int LX, int TY>
+template <bool FWD, typename R, int LX, int TY, int XV = x_vals(LX / 2)>
 hipError_t x_one(const void* in, void* out, int nx, int ny, int nsig, const void* tw, hipStream_t s)
 {
     if constexpr (TY == 0 || x_tile_ok<R, LX, TY>()) {
-        using S = XPassShape<R, LX, TY>;
+        using S = XPassShape<R, LX, TY, XV>;
         const long long rows = (long long)nsig * ny;
         if (2 * nx > LX || rows > 0x7fffffffLL) return hipErrorInvalidValue;
         const dim3 grid((unsigned)((rows + S::TY - 1) / S::TY));
         const FastDiv dny = FastDiv::make((unsigned)ny);
         if constexpr (FWD) {
-            hipError_t e = ensure_lds_limit((const void*)k_xfwd<R, LX, TY>, (int)S::LDS);
+            hipError_t e = ensure_lds_limit((const void*)k_xfwd<R, LX, TY, XV>, (int)S::LDS);
             if (e != hipSuccess) return e;
-            hipLaunchKernelGGL((k_xfwd<R, LX, TY>), grid, dim3(S::NT), S::LDS, s, (const R*)in, (cpx<R>*)out,
+            hipLaunchKernelGGL((k_xfwd<R, LX, TY, XV>), grid, dim3(S::NT), S::LDS, s, (const R*)in, (cpx<R>*)out,
                                nx, ny, (int)rows, dny, (const cpx<R>*)tw);
         } else {
             hipError_t e = ensure_lds_limit((const void*)k_xinv<R, LX, TY>, (int)S::LDS);
@@ -41,17 +41,17 @@ hipError_t x_one(const void* in, void* out, int nx, int ny, int nsig, const void
     return hipErrorInvalidValue;
 }
 
-template <bool FWD, typename R, int LX>
+template <bool FWD, typename R, int LX, int XV = x_vals(LX / 2)>
 hipError_t x_ty(int ty, const void* in, void* out, int nx, int ny, int nsig, const void* tw, hipStream_t s)
 {
     switch (ty) {
-    case 0: return x_one<FWD, R, LX, 0>(in, out, nx, ny, nsig, tw, s);
-    case 4: return x_one<FWD, R, LX, 4>(in, out, nx, ny, nsig, tw, s);
-    case 8: return x_one<FWD, R, LX, 8>(in, out, nx, ny, nsig, tw, s);
-    case 12: return x_one<FWD, R, LX, 12>(in, out, nx, ny, nsig, tw, s);
-    case 16: return x_one<FWD, R, LX, 16>(in, out, nx, ny, nsig, tw, s);
-    case 24: return x_one<FWD, R, LX, 24>(in, out, nx, ny, nsig, tw, s);
-    case 32: return x_one<FWD, R, LX, 32>(in, out, nx, ny, nsig, tw, s);
+    case 0: return x_one<FWD, R, LX, 0, XV>(in, out, nx, ny, nsig, tw, s);
+    case 4: return x_one<FWD, R, LX, 4, XV>(in, out, nx, ny, nsig, tw, s);
+    case 8: return x_one<FWD, R, LX, 8, XV>(in, out, nx, ny, nsig, tw, s);
+    case 12: return x_one<FWD, R, LX, 12, XV>(in, out, nx, ny, nsig, tw, s);
+    case 16: return x_one<FWD, R, LX, 16, XV>(in, out, nx, ny, nsig, tw, s);
+    case 24: return x_one<FWD, R, LX, 24, XV>(in, out, nx, ny, nsig, tw, s);
+    case 32: return x_one<FWD, R, LX, 32, XV>(in, out, nx, ny, nsig, tw, s);
     default: return hipErrorInvalidValue;
     }
 }
@@ -81,7 +81,7 @@ template <int LX>
 static hipError_t xtab_t(const double* in, void* out, int nx, int ny, long long nrows, const void* tw,
                          hipStream_t s)
 {
-    using S = XPassShape<double, LX, 0>;
+    using S = XTabShape<LX>;
     hipError_t e = ensure_lds_limit((const void*)k_xtab<LX, 0>, (int)S::LDS);
     if (e != hipSuccess) return e;
     if (nrows > 0x7fffffffLL) return hipErrorInvalidValue;
@@ -117,14 +117,17 @@ bool x_tile_supported(bool fp64, int LX, int ty)
     if (ty == 0) return true;
     if (ty != 4 && ty != 8 && ty != 12 && ty != 16 && ty != 24 && ty != 32) return false;
     const int M = LX / 2;
-    const int V = fft_vals(M), GT = M / V;
+    const int V = x_vals(M), GT = M / V;
     const size_t lds = (fp64 ? 16 : 8) * (size_t)ty * (size_t)(fft_region(M) | 1);
     return GT * ty <= 1024 && GT * ty >= 64 && lds <= 163840;
 }
 
 hipError_t launch_xfwd(bool fp64, int LX, const void* in, void* out, int nx, int ny, int nsig,
-                       const void* twx, hipStream_t s, int ty)
+                       const void* twx, hipStream_t s, int ty, bool for_gradient)
 {
+    // FP32 spectra of the thickness gradient in their own order of operations (see x_vals)
+    if (!fp64 && for_gradient && LX == 512)
+        return x_ty<true, float, 512, fft_vals(256)>(ty, in, out, nx, ny, nsig, twx, s);
     if (fp64) return x_lx<true, double>(LX, ty, in, out, nx, ny, nsig, twx, s);
     return x_lx<true, float>(LX, ty, in, out, nx, ny, nsig, twx, s);
 }

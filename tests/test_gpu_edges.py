@@ -119,3 +119,20 @@ def test_fused_threads_per_block_match_bruteforce(nx, ny, nz, B, fp64):
         ref = oracle.field(nx, ny, wl.dx, wl.dy, wl.z_bottom[0], wl.thickness[0], mused[b])
         assert rel_err(h[b], ref) < (1e-10 if fp64 else 1e-5), b
     plan.destroy()
+
+
+# x passes of 256-point transforms (16 values per lane), every tile height
+@pytest.mark.parametrize("fp64", [False, True], ids=["fp32", "fp64"])
+@pytest.mark.parametrize("nx,ny,nz", [(129, 3, 2), (256, 5, 1), (200, 7, 3), (255, 1, 1)])
+def test_x_passes_of_256_points_match_bruteforce(nx, ny, nz, fp64):
+    wl = W.small_case(nx, ny, nz, seed=1800 + nx, batch=2)
+    plan = plan_for(wl, flags=hfd.HFD_FP64 if fp64 else hfd.HFD_FP32)
+    refs = None
+    for ty in (0, 4, 8, 12, 16, 24, 32):
+        plan.set_path(2, 1, ty)
+        h, mused = run_field(plan, wl.m)
+        if refs is None:
+            refs = [oracle.field(nx, ny, wl.dx, wl.dy, wl.z_bottom[0], wl.thickness[0], mu) for mu in mused]
+        for b in range(2):
+            assert rel_err(h[b], refs[b]) < (1e-10 if fp64 else 1e-5), (ty, b)
+    plan.destroy()
