@@ -8,6 +8,7 @@ raises; there is no CPU fallback.
 from __future__ import annotations
 
 import ctypes
+import functools
 import os
 from typing import Optional, Sequence
 
@@ -308,7 +309,10 @@ class Plan:
             pass
 
 
+@functools.lru_cache(maxsize=None)
 def _autograd():
+    """DemagField, made once (torch is imported on first use): a class per call cost
+    30 us of host time."""
     import torch
 
     class DemagField(torch.autograd.Function):
