@@ -131,9 +131,9 @@ __device__ __forceinline__ void real_split_inv(cpx<R>& a, cpx<R>& b, cpx<R> w, b
 // large ones.  All global accesses of a thread are requested together, and
 // the indices are divided out once per thread; with the split in the rows (one
 // more LDS round trip) and an index division per element the two passes of
-// 64 states of 512 x 512 x 4 took 932 + 1360 us, now 578 + 569 (2.4 GB each at
+// 64 states of 512 x 512 x 4 took 932 + 1360 us, now 620 + 567 (2.4 GB each at
 // 4.2 TB/s; a copy runs at 4.9), those of one 256 x 256 x 8 state 9.1 + 8.7,
-// now 6.8 + 6.2.
+// now 6.6 + 6.2.
 // ---------------------------------------------------------------------------
 template <typename R, int LX, int TYO = 0, int XV = x_vals(LX / 2)>
 __global__ __launch_bounds__((XPassShape<R, LX, TYO, XV>::NT), (XPassShape<R, LX, TYO, XV>::WPE)) void k_xfwd(
