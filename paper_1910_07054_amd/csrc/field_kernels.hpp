@@ -27,9 +27,8 @@ namespace hfd {
 // Values per lane of the x passes' transforms.  16 for 256 points (rows of 129 to 256
 // cells): two radix-16 passes with one exchange instead of 8 8 4 with two, and half
 // the threads per row, 16 states of 256 x 256 x 10 118 + 100 -> 91 + 82 us, 256 x 256 x 8
-// 8.1 + 7.3 -> 6.6 + 6.5, in FP64 9.9 + 10.0 -> 9.1 + 8.2.  For 128 points it pays with many
-// rows only (8 states of 100 x 60 x 12 9.7 + 8.3 -> 8.2 + 7.4, one of 128 x 128 x 8 3.5 + 3.3 ->
-// 3.9 + 3.6).  Forward passes whose spectra feed the thickness gradient keep 8 there
+// 8.1 + 7.3 -> 6.6 + 6.5, in FP64 9.9 + 10.0 -> 9.1 + 8.2.  128 points take 16 with many
+// rows (x_lx).  Forward passes whose spectra feed the thickness gradient keep 8 there
 // (XV below): it is an FP64 result of FP32 spectra, and another order of their
 // roundings moves its seventh digit.
 __host__ __device__ constexpr int x_vals(int M) { return M == 256 ? 16 : fft_vals(M); }
@@ -204,12 +203,12 @@ __global__ __launch_bounds__((XPassShape<R, LX, TYO, XV>::NT), (XPassShape<R, LX
 // all its pairs (k, M - k) of one row, splits them in registers and puts them
 // into LDS, where the row's group finds its first radix pass.
 // ---------------------------------------------------------------------------
-template <typename R, int LX, int TYO = 0>
-__global__ __launch_bounds__((XPassShape<R, LX, TYO>::NT), (XPassShape<R, LX, TYO>::WPE)) void k_xinv(
+template <typename R, int LX, int TYO = 0, int XV = x_vals(LX / 2)>
+__global__ __launch_bounds__((XPassShape<R, LX, TYO, XV>::NT), (XPassShape<R, LX, TYO, XV>::WPE)) void k_xinv(
     const cpx<R>* __restrict__ in, R* __restrict__ out, int nx, int ny, int nrows, FastDiv dny,
     const cpx<R>* __restrict__ twx)
 {
-    using S = XPassShape<R, LX, TYO>;
+    using S = XPassShape<R, LX, TYO, XV>;
     constexpr int M = S::M, GT = S::GT, NG = S::NG, TY = S::TY, RS = S::RS, RPG = S::RPG;
     constexpr int KI = S::KI, KS = S::KS;
     extern __shared__ __align__(16) unsigned char smem_raw[];

@@ -9,17 +9,17 @@ namespace {
 
 // a tile size is compiled for a length when its block fits (<= 1024 threads,
 // <= 160 KB of LDS) and it is not the default one
-template <typename R, int LX, int TY>
+template <typename R, int LX, int TY, int XV>
 constexpr bool x_tile_ok()
 {
-    using S = XPassShape<R, LX, TY>;
+    using S = XPassShape<R, LX, TY, XV>;
     return S::GT * TY <= 1024 && S::GT * TY >= 64 && S::LDS <= 163840;
 }
 
 template <bool FWD, typename R, int LX, int TY, int XV = x_vals(LX / 2)>
 hipError_t x_one(const void* in, void* out, int nx, int ny, int nsig, const void* tw, hipStream_t s)
 {
-    if constexpr (TY == 0 || x_tile_ok<R, LX, TY>()) {
+    if constexpr (TY == 0 || x_tile_ok<R, LX, TY, XV>()) {
         using S = XPassShape<R, LX, TY, XV>;
         const long long rows = (long long)nsig * ny;
         if (2 * nx > LX || rows > 0x7fffffffLL) return hipErrorInvalidValue;
@@ -31,9 +31,9 @@ hipError_t x_one(const void* in, void* out, int nx, int ny, int nsig, const void
             hipLaunchKernelGGL((k_xfwd<R, LX, TY, XV>), grid, dim3(S::NT), S::LDS, s, (const R*)in, (cpx<R>*)out,
                                nx, ny, (int)rows, dny, (const cpx<R>*)tw);
         } else {
-            hipError_t e = ensure_lds_limit((const void*)k_xinv<R, LX, TY>, (int)S::LDS);
+            hipError_t e = ensure_lds_limit((const void*)k_xinv<R, LX, TY, XV>, (int)S::LDS);
             if (e != hipSuccess) return e;
-            hipLaunchKernelGGL((k_xinv<R, LX, TY>), grid, dim3(S::NT), S::LDS, s, (const cpx<R>*)in, (R*)out,
+            hipLaunchKernelGGL((k_xinv<R, LX, TY, XV>), grid, dim3(S::NT), S::LDS, s, (const cpx<R>*)in, (R*)out,
                                nx, ny, (int)rows, dny, (const cpx<R>*)tw);
         }
         return hipGetLastError();
@@ -56,17 +56,24 @@ hipError_t x_ty(int ty, const void* in, void* out, int nx, int ny, int nsig, con
     }
 }
 
+// 128-point transforms (rows of 65 to 128 cells): 16 values per lane, two passes instead
+// of 8 8 2, pay from 8192 rows on (24576 rows: 10.4 + 9.0 -> 8.8 + 8.3 us; 12288: 7.1 + 6.9 ->
+// 6.8 + 6.6; 6144: 4.4 + 4.0 -> 4.4 + 4.2; 3072: 3.4 + 3.4 -> 3.8 + 3.7); tiles of 4 rows
+// would be half a wave then.  narrow: the thickness gradient's spectra (see x_vals).
 template <bool FWD, typename R>
 hipError_t x_lx(int LX, int ty, const void* in, void* out, int nx, int ny, int nsig, const void* tw,
-                hipStream_t s)
+                hipStream_t s, bool narrow = false)
 {
+    const bool wide = !narrow && (long long)nsig * ny >= 8192;
     switch (LX) {
     case 8: return x_ty<FWD, R, 8>(ty, in, out, nx, ny, nsig, tw, s);
     case 16: return x_ty<FWD, R, 16>(ty, in, out, nx, ny, nsig, tw, s);
     case 32: return x_ty<FWD, R, 32>(ty, in, out, nx, ny, nsig, tw, s);
     case 64: return x_ty<FWD, R, 64>(ty, in, out, nx, ny, nsig, tw, s);
     case 128: return x_ty<FWD, R, 128>(ty, in, out, nx, ny, nsig, tw, s);
-    case 256: return x_ty<FWD, R, 256>(ty, in, out, nx, ny, nsig, tw, s);
+    case 256:
+        if (wide && ty != 4) return x_ty<FWD, R, 256, 16>(ty, in, out, nx, ny, nsig, tw, s);
+        return x_ty<FWD, R, 256>(ty, in, out, nx, ny, nsig, tw, s);
     case 512: return x_ty<FWD, R, 512>(ty, in, out, nx, ny, nsig, tw, s);
     case 1024: return x_ty<FWD, R, 1024>(ty, in, out, nx, ny, nsig, tw, s);
     case 2048: return x_ty<FWD, R, 2048>(ty, in, out, nx, ny, nsig, tw, s);
@@ -129,7 +136,7 @@ hipError_t launch_xfwd(bool fp64, int LX, const void* in, void* out, int nx, int
     if (!fp64 && for_gradient && LX == 512)
         return x_ty<true, float, 512, fft_vals(256)>(ty, in, out, nx, ny, nsig, twx, s);
     if (fp64) return x_lx<true, double>(LX, ty, in, out, nx, ny, nsig, twx, s);
-    return x_lx<true, float>(LX, ty, in, out, nx, ny, nsig, twx, s);
+    return x_lx<true, float>(LX, ty, in, out, nx, ny, nsig, twx, s, for_gradient);
 }
 
 hipError_t launch_xinv(bool fp64, int LX, const void* in, void* out, int nx, int ny, int nsig,

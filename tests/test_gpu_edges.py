@@ -136,3 +136,22 @@ def test_x_passes_of_256_points_match_bruteforce(nx, ny, nz, fp64):
         for b in range(2):
             assert rel_err(h[b], refs[b]) < (1e-10 if fp64 else 1e-5), (ty, b)
     plan.destroy()
+
+
+# 128-point x transforms on both sides of the row count from which a lane takes 16 values
+@pytest.mark.parametrize("fp64", [False, True], ids=["fp32", "fp64"])
+@pytest.mark.parametrize("nx,ny,nz,B", [(128, 2, 2, 700), (65, 3, 1, 911), (100, 1, 3, 910)])
+def test_x_passes_of_128_points_many_rows(nx, ny, nz, B, fp64):
+    wl = W.small_case(nx, ny, nz, seed=1900 + nx, batch=1)
+    m = np.stack([np.roll(wl.m[0], b, axis=-1) for b in range(B)])
+    plan = hfd.Plan(nx, ny, wl.dx, wl.dy, wl.thickness[0], wl.z_bottom[0], batch_max=B,
+                    flags=hfd.HFD_FP64 if fp64 else hfd.HFD_FP32)
+    refs = {}
+    for ty in (0, 4, 8, 16, 24, 32):
+        plan.set_path(B, 1, ty)
+        h, mused = run_field(plan, m)
+        for b in (0, B // 2, B - 1):
+            if b not in refs:
+                refs[b] = oracle.field(nx, ny, wl.dx, wl.dy, wl.z_bottom[0], wl.thickness[0], mused[b])
+            assert rel_err(h[b], refs[b]) < (1e-10 if fp64 else 1e-5), (ty, b)
+    plan.destroy()
