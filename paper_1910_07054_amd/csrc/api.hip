@@ -17,6 +17,7 @@
 #include <vector>
 
 #include "../../include/hfd.h"
+#include "derivative_sizes.hpp"
 #include "launch.hpp"
 
 using namespace hfd;
@@ -179,12 +180,12 @@ struct hfd_plan_s {
     void* Hh = nullptr;
     size_t x1_bytes = 0, mh_bytes = 0;
     // thickness-derivative data
-    void* D = nullptr;          // [QX][nzeta_max][6][QY] plan precision, one offset table
+    void* D = nullptr;          // [QX][dsize.slots][6][QY] plan precision, one offset table
     int* itab = nullptr;        // [G][itab_stride] interface positions and D slots (k_tgrad)
     int itab_stride = 0;
     int ni_max = 0;             // most interface positions of a stack
-    double* zeta_dev = nullptr; // [tables][nzeta_max]
-    int nzeta_max = 0;
+    double* zeta_dev = nullptr; // [tables][dsize.slots]
+    DerivativeSizes dsize;      // what D and zeta_dev hold
     std::vector<int> nzeta;     // per table (one shared table when stored, else per group)
     std::vector<int> dgroup;    // first stack of each table's group, then G
     std::vector<double> zeta_host;
@@ -706,7 +707,7 @@ constexpr long long kRecomputeBytes = 256LL << 20;
 // buffers are allocated before the old ones are released, so a failure leaves
 // the previous buffers in place (the plan is then marked not ready by the
 // caller).  Buffers only grow: a geometry with fewer distinct offsets keeps
-// the allocated stride nzeta_max.
+// the allocated stride dsize.slots.
 hfd_status setup_derivatives(hfd_plan p, hipStream_t s)
 {
     std::vector<double> zeta;
@@ -726,17 +727,19 @@ hfd_status setup_derivatives(hfd_plan p, hipStream_t s)
         if (slot) (void)hipFree(slot);
         slot = fresh;
     };
-    if (nmax > p->nzeta_max || !p->D) {
-        const long long per_table = (long long)nmax * 6 * p->QX * p->QY;
+    const DerivativeSizes want = derivative_sizes(p->dsize, (int)count.size(), nmax);
+    if (want.slots > p->dsize.slots) {
+        const long long per_table = (long long)want.slots * 6 * p->QX * p->QY;
         void* nD = nullptr;
-        double* nz_dev = nullptr;
         HFD_TRY(dev_alloc(&nD, (size_t)per_table * p->rsz, "derivative tensor"));
-        hfd_status st = dev_alloc(&nz_dev, sizeof(double) * count.size() * (size_t)nmax,
-                                  "derivative offsets");
-        if (st) { (void)hipFree(nD); return st; }
         swap_in(p->D, nD);
+        p->dsize.slots = want.slots;
+    }
+    if (want.offsets > p->dsize.offsets) {
+        double* nz_dev = nullptr;
+        HFD_TRY(dev_alloc(&nz_dev, sizeof(double) * (size_t)want.offsets, "derivative offsets"));
         swap_in(p->zeta_dev, nz_dev);
-        p->nzeta_max = nmax;
+        p->dsize.offsets = want.offsets;
     }
     if (!p->itab) HFD_TRY(dev_alloc(&p->itab, sizeof(int) * itab.size(), "interface table"));
     p->itab_stride = itab_layout(p->nz).stride;
@@ -761,11 +764,11 @@ hfd_status setup_derivatives(hfd_plan p, hipStream_t s)
         HFD_HIP(hipMemcpyAsync(p->dscale, sc.data(), sizeof(double) * chunk, hipMemcpyHostToDevice, s));
         p->dchunk = chunk;
     }
-    // offsets of table k at k * nzeta_max (the allocated stride, which stays
+    // offsets of table k at k * dsize.slots (the allocated stride, which stays
     // larger than nmax when a new geometry has fewer distinct offsets)
-    p->zeta_host.assign(count.size() * (size_t)p->nzeta_max, 0.0);
+    p->zeta_host.assign(count.size() * (size_t)p->dsize.slots, 0.0);
     for (size_t k = 0; k < count.size(); ++k)
-        for (int i = 0; i < count[k]; ++i) p->zeta_host[k * p->nzeta_max + i] = zeta[k * nmax + i];
+        for (int i = 0; i < count[k]; ++i) p->zeta_host[k * p->dsize.slots + i] = zeta[k * nmax + i];
     p->itab_host = itab;
     p->ni_max = 0;
     for (int g = 0; g < p->G; ++g)
@@ -799,11 +802,11 @@ hfd_status compute_derivatives(hfd_plan p, int g, hipStream_t s)
     char* dst = (char*)p->D;
     for (int z0 = 0; z0 < nzt; z0 += p->dchunk) {
         const int nc = std::min(p->dchunk, nzt - z0);
-        HFD_HIP(launch_dtensor_real(p->dW, p->zeta_dev + (size_t)g * p->nzeta_max + z0, nc, p->nx,
+        HFD_HIP(launch_dtensor_real(p->dW, p->zeta_dev + (size_t)g * p->dsize.slots + z0, nc, p->nx,
                                     p->ny, p->dx, p->dy, s));
         HFD_HIP(launch_xtab(p->Lx, p->dW, p->dF, p->nx, p->ny, nc * 6, p->twx64, s));
         HFD_HIP(launch_ytab(p->fp64, p->dF, dst, p->dscale, nc, 6, p->M, p->ny, p->Ly, p->QX, p->QY, z0,
-                            p->nzeta_max, 1, p->twy64, s));
+                            p->dsize.slots, 1, p->twy64, s));
     }
     return HFD_OK;
 }
@@ -1212,9 +1215,9 @@ hfd_status hfd_demag_vjp(hfd_plan p, const void* m, const void* grad_h, void* gr
     if (!grad_m && !grad_thickness) return fail(HFD_EINVAL, "grad_m and grad_thickness are both NULL");
     if (p->eq3d && grad_thickness)
         return fail(HFD_ENOTSUP, "thickness gradients need the non-equidistant plan (no HFD_EQUIDISTANT)");
-    if (grad_thickness && (long long)p->nzeta_max * 6 * p->QY * (long long)p->rsz >= (1LL << 31))
+    if (grad_thickness && (long long)p->dsize.slots * 6 * p->QY * (long long)p->rsz >= (1LL << 31))
         return fail(HFD_ENOTSUP, "one kx row of the thickness-derivative table exceeds 2 GiB (" +
-                                     std::to_string(p->nzeta_max) + " offsets): use fewer stacks per "
+                                     std::to_string(p->dsize.slots) + " offsets): use fewer stacks per "
                                      "plan or leave out HFD_STORE_DTENSOR");
     if (grad_m) HFD_TRY(check_field_args(p, grad_h, grad_m, batch, "grad_h", "grad_m"));
     if (grad_thickness) {
@@ -1247,7 +1250,7 @@ hfd_status hfd_demag_vjp(hfd_plan p, const void* m, const void* grad_h, void* gr
     }
     if (stored) {
         HFD_HIP(launch_tgrad(p->fp64, p->Mh, p->Hh, p->nz, p->M, p->Ly, 0, batch, p->Q, p->qcs,
-                             p->qslot, p->D, p->nzeta_max, p->itab, p->itab_stride, p->ni_max, p->lp, bpg, p->QX,
+                             p->qslot, p->D, p->dsize.slots, p->itab, p->itab_stride, p->ni_max, p->lp, bpg, p->QX,
                              p->QY, p->partial, s));
     } else {
         // recompute the derivative tensor of one group of stacks at a time
@@ -1255,7 +1258,7 @@ hfd_status hfd_demag_vjp(hfd_plan p, const void* m, const void* grad_h, void* gr
             const int g0 = p->dgroup[k], g1 = p->dgroup[k + 1];
             HFD_TRY(compute_derivatives(p, (int)k, s));
             HFD_HIP(launch_tgrad(p->fp64, p->Mh, p->Hh, p->nz, p->M, p->Ly, g0 * bpg, (g1 - g0) * bpg,
-                                 p->Q, p->qcs, p->qslot, p->D, p->nzeta_max, p->itab,
+                                 p->Q, p->qcs, p->qslot, p->D, p->dsize.slots, p->itab,
                                  p->itab_stride, p->ni_max, p->lp, bpg, p->QX, p->QY, p->partial, s));
         }
     }

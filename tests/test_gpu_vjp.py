@@ -233,3 +233,28 @@ def test_thickness_gradient_waves_per_tile(nz, B, fp64):
         err = np.abs(gt[b] - ref).max() / np.abs(ref).max()
         assert err < (1e-10 if fp64 else 2e-5), (b, err)
     plan.destroy()
+
+
+def test_thickness_gradient_after_reset_to_more_offset_tables():
+    """12 stacks that share one offset table (4 different ones, each three times),
+    set to 12 unrelated ones: as many offsets per table, but three tables (one
+    holds 42 offsets at this size and 4 layers have 11).  The gradients are those
+    of a plan created with the second geometry, bit for bit."""
+    import torch
+    nx = ny = 260
+    nz, G = 4, 12
+    rng = np.random.default_rng(47)
+    t2 = rng.uniform(0.5, 3.0, size=(G, nz))
+    t1 = np.repeat(rng.uniform(0.5, 3.0, size=(G // 3, nz)), 3, axis=0)
+    m = torch.from_numpy(rng.standard_normal((G, 3, nz, ny, nx)).astype(np.float32)).cuda()
+    g = torch.from_numpy(rng.standard_normal((G, 3, nz, ny, nx)).astype(np.float32)).cuda()
+    plan = hfd.Plan(nx, ny, 2.0, 2.0, t1, batch_max=G)
+    plan.vjp(m, g, want_m=False)
+    plan.set_thickness(t2)
+    got = plan.vjp(m, g, want_m=False)[1].cpu()
+    plan.destroy()
+    fresh = hfd.Plan(nx, ny, 2.0, 2.0, t2, batch_max=G)
+    ref = fresh.vjp(m, g, want_m=False)[1].cpu()
+    fresh.destroy()
+    assert torch.isfinite(ref).all()
+    assert torch.equal(got, ref)
