@@ -1054,7 +1054,7 @@ hfd_status hfd_setup_tensor(hfd_plan* out, int nx, int ny, double dx, double dy,
         p->qcs = (long long)p->nslot * 5 * p->QY;
         // kernels read the slot table through 32-bit byte offsets from the
         // start of a kx row (the packed column: of the first two rows)
-        if (2 * p->qcs * (long long)p->rsz >= (1LL << 31)) {
+        if (2 * p->qcs * (long long)p->rsz >= kDescriptorBytes) {
             delete p;
             return fail(HFD_ENOTSUP, "one kx row of the tensor table (n_geom * nz (nz + 1) / 2 pairs) exceeds "
                                      "2 GiB: use fewer stacks per plan");
@@ -1215,7 +1215,7 @@ hfd_status hfd_demag_vjp(hfd_plan p, const void* m, const void* grad_h, void* gr
     if (!grad_m && !grad_thickness) return fail(HFD_EINVAL, "grad_m and grad_thickness are both NULL");
     if (p->eq3d && grad_thickness)
         return fail(HFD_ENOTSUP, "thickness gradients need the non-equidistant plan (no HFD_EQUIDISTANT)");
-    if (grad_thickness && (long long)p->dsize.slots * 6 * p->QY * (long long)p->rsz >= (1LL << 31))
+    if (grad_thickness && !derivative_rows_fit(1, p->dsize.slots, p->QY, (long long)p->rsz))
         return fail(HFD_ENOTSUP, "one kx row of the thickness-derivative table exceeds 2 GiB (" +
                                      std::to_string(p->dsize.slots) + " offsets): use fewer stacks per "
                                      "plan or leave out HFD_STORE_DTENSOR");

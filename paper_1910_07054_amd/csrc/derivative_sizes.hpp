@@ -25,4 +25,16 @@ inline DerivativeSizes derivative_sizes(DerivativeSizes have, int tables, int mo
     return s;
 }
 
+// Bytes from the start of a row of the derivative spectra ([slots][6][QY] values)
+// that a buffer descriptor reaches: offsets stay below 2^31, as those of the
+// tensor table do.  One row per descriptor is what any call needs (more is
+// refused); the staged kernel reads the rows kx = 0 and kx = Lx/2 of its packed
+// column through one descriptor, so that it takes calls where both fit, and the
+// unstaged kernel, with a descriptor per row, takes the others.
+constexpr long long kDescriptorBytes = 1LL << 31;
+inline bool derivative_rows_fit(int rows, long long slots, long long QY, long long value_bytes)
+{
+    return rows * slots * 6 * QY * value_bytes < kDescriptorBytes;
+}
+
 }  // namespace hfd

@@ -36,6 +36,7 @@
 // dz_p/dt_k = [k < r_p].  D is stored for |zeta| only: dPsi/dz is odd in zeta
 // for xx, yy, zz, xy and even for xz, yz, so D(-zeta) is D(zeta) with the
 // first four negated (the table entry of a pair carries the sign).
+#include "derivative_sizes.hpp"
 #include "field_kernels.hpp"
 #include "launch.hpp"
 
@@ -771,6 +772,7 @@ static hipError_t tgrad_r(const void* Mh, const void* Gh, int nz, int M, int LY,
     constexpr size_t kMax = 163840;
     int waves = tgrad_waves(nz, nblk);
     if (tgrad_lds<R>(waves, nz, ni_max) > kMax) waves = tgrad_lds<R>(2, nz, ni_max) <= kMax ? 2 : 0;
+    if (!derivative_rows_fit(2, nzt, QY, sizeof(R))) waves = 0;
     if (waves > 0) {
         const size_t lds = tgrad_lds<R>(waves, nz, ni_max);
         const hipError_t e = ensure_lds_limit((const void*)k_tgrad<R>, lds > 65536 ? (int)kMax : 0);
@@ -795,10 +797,9 @@ hipError_t launch_tgrad(bool fp64, const void* Mh, const void* Gh, int nz, int M
     if (nz < 1 || nz > 64 || ni_max < 1 || ni_max > 2 * nz || nb < 1 || bpg < 1 || nb % bpg || LY < 2 || (LY & (LY - 1)))
         return hipErrorInvalidValue;
     (void)QX;  // D and Q rows are addressed through nzt, qcs and QY
-    // one row of D or Q is a buffer with 32-bit byte offsets
+    // one row of D, two of Q (the packed column's) per descriptor; tgrad_r on two rows of D
     const long long rsz = fp64 ? 8 : 4;
-    if ((long long)nzt * 6 * QY * rsz >= (1LL << 31) || qcs * rsz >= (1LL << 31))
-        return hipErrorInvalidValue;
+    if (!derivative_rows_fit(1, nzt, QY, rsz) || 2 * qcs * rsz >= kDescriptorBytes) return hipErrorInvalidValue;
     const int ntiles = tgrad_tiles(M, LY);
     const long long nblk = (long long)((ntiles + 7) / 8) * 8 * nb;
     if (nblk > 0x7fffffffLL) return hipErrorInvalidValue;

@@ -44,3 +44,18 @@ def test_offset_tables_fit_after_every_reset(tmp_path, resets):
         assert out[2 * k] >= max(n, slots)
         assert out[2 * k + 1] >= max(t * out[2 * k], offsets)
         slots, offsets = out[2 * k], out[2 * k + 1]
+
+
+# (slots, Ly / 2 + 1, bytes per value): whether one row and whether two rows lie
+# within 2 GiB; 21835 slots of 2049 FP32 values pass 1 GiB, 43670 pass 2 GiB
+ROWS = [(21834, 2049, 4, 1, 1), (21835, 2049, 4, 1, 0), (43669, 2049, 4, 1, 0), (43670, 2049, 4, 0, 0),
+        (10917, 2049, 8, 1, 1), (10918, 2049, 8, 1, 0), (10, 5, 4, 1, 1), (1 << 30, 2049, 8, 0, 0)]
+
+
+def test_rows_of_the_spectra_within_a_descriptor(tmp_path):
+    body = "".join(f'printf("%d %d\\n", (int)derivative_rows_fit(1, {s}, {q}, {b}), '
+                   f'(int)derivative_rows_fit(2, {s}, {q}, {b}));\n' for s, q, b, _, _ in ROWS)
+    out = _run(tmp_path, body)
+    assert out == [v for r in ROWS for v in r[3:]]
+    for s, q, b, one, two in ROWS:
+        assert (6 * s * q * b < 2**31, 12 * s * q * b < 2**31) == (bool(one), bool(two))

@@ -258,3 +258,23 @@ def test_thickness_gradient_after_reset_to_more_offset_tables():
     fresh.destroy()
     assert torch.isfinite(ref).all()
     assert torch.equal(got, ref)
+
+
+def test_thickness_gradient_with_long_derivative_rows():
+    """42 stacks of 32 layers, whose stored table has 22177 offsets: two rows of it
+    (the packed column's) are over 2 GiB and one is not, so that the kernel with a
+    descriptor per row takes the call.  Against a plan without the stored table,
+    which goes through short tables and the staged kernel; the two differ in the
+    order of FP64 sums."""
+    import torch
+    nx, ny, nz, G = 3, 2048, 32, 42
+    rng = np.random.default_rng(48)
+    t = rng.uniform(0.5, 3.0, size=(G, nz))
+    m = torch.from_numpy(rng.standard_normal((G, 3, nz, ny, nx)).astype(np.float32)).cuda()
+    g = torch.from_numpy(rng.standard_normal((G, 3, nz, ny, nx)).astype(np.float32)).cuda()
+    gt = []
+    for flags in (hfd.HFD_STORE_DTENSOR, hfd.HFD_FP32):
+        plan = hfd.Plan(nx, ny, 2.0, 2.0, t, batch_max=G, flags=flags)
+        gt.append(plan.vjp(m, g, want_m=False)[1].cpu().numpy())
+        plan.destroy()
+    assert np.abs(gt[0] - gt[1]).max() < 1e-9 * np.abs(gt[1]).max()
