@@ -24,14 +24,24 @@
 
 namespace hfd {
 
-// Values per lane of the x passes' transforms.  16 for 256 points (rows of 129 to 256
-// cells): two radix-16 passes with one exchange instead of 8 8 4 with two, and half
-// the threads per row, 16 states of 256 x 256 x 10 118 + 100 -> 91 + 82 us, 256 x 256 x 8
-// 8.1 + 7.3 -> 6.6 + 6.5, in FP64 9.9 + 10.0 -> 9.1 + 8.2.  128 points take 16 with many
-// rows (x_lx).  Forward passes whose spectra feed the thickness gradient keep 8 there
-// (XV below): it is an FP64 result of FP32 spectra, and another order of their
-// roundings moves its seventh digit.
-__host__ __device__ constexpr int x_vals(int M) { return M == 256 ? 16 : fft_vals(M); }
+// Values per lane of the x passes' transforms, one choice per length, precision and
+// direction: the order of a transform's roundings follows from it, and a state's
+// results depend neither on the batch it is in nor on which of its gradients are
+// asked for.  256 points (rows of 129 to 256 cells) take 16 in inverse passes and in
+// FP64: two radix-16 passes with one exchange instead of 8 8 4 with two, and half the
+// threads per row.  At equal tile heights, 8 and 16 values: 256 x 256 x 8 (24 rows) forward
+// 6.8, 6.3 us, inverse 6.1, 5.4, FP64 (8 rows) 9.7, 8.9 and 8.2, 7.1; 32 layers (32 rows)
+// 18.6, 16.7 and 19.4, 18.2; 16 states of 10 layers (32 rows) 94, 91 and 78, 79.  FP32
+// forward passes stay at 8: one kernel makes the spectra of the field, of its transpose
+// and of the thickness gradient, whose FP64 values stay what they were (16 are no more
+// accurate, and move its seventh digit).  At 128 points 16 values are slower below 8192 rows
+// (128 x 128 x 8: 3.3 + 3.2 us against 3.7 + 3.5) and a little faster above (8 states: 9.5 + 8.3
+// against 8.7 + 8.3), so 8 for all.
+template <typename R, bool FWD>
+__host__ __device__ constexpr int x_vals(int M)
+{
+    return M == 256 && (sizeof(R) == 8 || !FWD) ? 16 : fft_vals(M);
+}
 
 // Rows are numbered flat over all signals (row r = signal r / ny, y = r % ny)
 // and a block takes TY consecutive rows, one wave or part of a wave per row,
@@ -39,7 +49,7 @@ __host__ __device__ constexpr int x_vals(int M) { return M == 256 ? 16 : fft_val
 // The transposed side of a pass moves TY consecutive y of one kx: TY = 16 rows
 // (8 in FP64) are one 128-byte line.  TYO = 0 picks that, or one wave of rows
 // if that is more, halved until the tile fits in 80 KB of LDS.
-template <typename R, int LX, int TYO = 0, int XV = x_vals(LX / 2)>
+template <typename R, int LX, int TYO, int XV>
 struct XPassShape {
     static constexpr int M = LX / 2;
     static constexpr int V = XV;
@@ -134,7 +144,7 @@ __device__ __forceinline__ void real_split_inv(cpx<R>& a, cpx<R>& b, cpx<R> w, b
 // 4.2 TB/s; a copy runs at 4.9), those of one 256 x 256 x 8 state 9.1 + 8.7,
 // now 6.6 + 6.2.
 // ---------------------------------------------------------------------------
-template <typename R, int LX, int TYO = 0, int XV = x_vals(LX / 2)>
+template <typename R, int LX, int TYO = 0, int XV = x_vals<R, true>(LX / 2)>
 __global__ __launch_bounds__((XPassShape<R, LX, TYO, XV>::NT), (XPassShape<R, LX, TYO, XV>::WPE)) void k_xfwd(
     const R* __restrict__ in, cpx<R>* __restrict__ out, int nx, int ny, int nrows, FastDiv dny,
     const cpx<R>* __restrict__ twx)
@@ -203,7 +213,7 @@ __global__ __launch_bounds__((XPassShape<R, LX, TYO, XV>::NT), (XPassShape<R, LX
 // all its pairs (k, M - k) of one row, splits them in registers and puts them
 // into LDS, where the row's group finds its first radix pass.
 // ---------------------------------------------------------------------------
-template <typename R, int LX, int TYO = 0, int XV = x_vals(LX / 2)>
+template <typename R, int LX, int TYO = 0, int XV = x_vals<R, false>(LX / 2)>
 __global__ __launch_bounds__((XPassShape<R, LX, TYO, XV>::NT), (XPassShape<R, LX, TYO, XV>::WPE)) void k_xinv(
     const cpx<R>* __restrict__ in, R* __restrict__ out, int nx, int ny, int nrows, FastDiv dny,
     const cpx<R>* __restrict__ twx)

@@ -32,7 +32,7 @@ bool x_tile_supported(bool fp64, int LX, int ty);
 hipError_t launch_xtab(int LX, const double* in, void* out, int nx, int ny, int nsig, const void* twx64,
                        hipStream_t s);
 hipError_t launch_xfwd(bool fp64, int LX, const void* in, void* out, int nx, int ny, int nsig,
-                       const void* twx, hipStream_t s, int ty = 0, bool for_gradient = false);
+                       const void* twx, hipStream_t s, int ty = 0);
 hipError_t launch_xinv(bool fp64, int LX, const void* in, void* out, int nx, int ny, int nsig,
                        const void* twx, hipStream_t s, int ty = 0);
 

@@ -16,9 +16,10 @@ constexpr bool x_tile_ok()
     return S::GT * TY <= 1024 && S::GT * TY >= 64 && S::LDS <= 163840;
 }
 
-template <bool FWD, typename R, int LX, int TY, int XV = x_vals(LX / 2)>
+template <bool FWD, typename R, int LX, int TY>
 hipError_t x_one(const void* in, void* out, int nx, int ny, int nsig, const void* tw, hipStream_t s)
 {
+    constexpr int XV = x_vals<R, FWD>(LX / 2);
     if constexpr (TY == 0 || x_tile_ok<R, LX, TY, XV>()) {
         using S = XPassShape<R, LX, TY, XV>;
         const long long rows = (long long)nsig * ny;
@@ -41,39 +42,32 @@ hipError_t x_one(const void* in, void* out, int nx, int ny, int nsig, const void
     return hipErrorInvalidValue;
 }
 
-template <bool FWD, typename R, int LX, int XV = x_vals(LX / 2)>
+template <bool FWD, typename R, int LX>
 hipError_t x_ty(int ty, const void* in, void* out, int nx, int ny, int nsig, const void* tw, hipStream_t s)
 {
     switch (ty) {
-    case 0: return x_one<FWD, R, LX, 0, XV>(in, out, nx, ny, nsig, tw, s);
-    case 4: return x_one<FWD, R, LX, 4, XV>(in, out, nx, ny, nsig, tw, s);
-    case 8: return x_one<FWD, R, LX, 8, XV>(in, out, nx, ny, nsig, tw, s);
-    case 12: return x_one<FWD, R, LX, 12, XV>(in, out, nx, ny, nsig, tw, s);
-    case 16: return x_one<FWD, R, LX, 16, XV>(in, out, nx, ny, nsig, tw, s);
-    case 24: return x_one<FWD, R, LX, 24, XV>(in, out, nx, ny, nsig, tw, s);
-    case 32: return x_one<FWD, R, LX, 32, XV>(in, out, nx, ny, nsig, tw, s);
+    case 0: return x_one<FWD, R, LX, 0>(in, out, nx, ny, nsig, tw, s);
+    case 4: return x_one<FWD, R, LX, 4>(in, out, nx, ny, nsig, tw, s);
+    case 8: return x_one<FWD, R, LX, 8>(in, out, nx, ny, nsig, tw, s);
+    case 12: return x_one<FWD, R, LX, 12>(in, out, nx, ny, nsig, tw, s);
+    case 16: return x_one<FWD, R, LX, 16>(in, out, nx, ny, nsig, tw, s);
+    case 24: return x_one<FWD, R, LX, 24>(in, out, nx, ny, nsig, tw, s);
+    case 32: return x_one<FWD, R, LX, 32>(in, out, nx, ny, nsig, tw, s);
     default: return hipErrorInvalidValue;
     }
 }
 
-// 128-point transforms (rows of 65 to 128 cells): 16 values per lane, two passes instead
-// of 8 8 2, pay from 8192 rows on (24576 rows: 10.4 + 9.0 -> 8.8 + 8.3 us; 12288: 7.1 + 6.9 ->
-// 6.8 + 6.6; 6144: 4.4 + 4.0 -> 4.4 + 4.2; 3072: 3.4 + 3.4 -> 3.8 + 3.7); tiles of 4 rows
-// would be half a wave then.  narrow: the thickness gradient's spectra (see x_vals).
 template <bool FWD, typename R>
 hipError_t x_lx(int LX, int ty, const void* in, void* out, int nx, int ny, int nsig, const void* tw,
-                hipStream_t s, bool narrow = false)
+                hipStream_t s)
 {
-    const bool wide = !narrow && (long long)nsig * ny >= 8192;
     switch (LX) {
     case 8: return x_ty<FWD, R, 8>(ty, in, out, nx, ny, nsig, tw, s);
     case 16: return x_ty<FWD, R, 16>(ty, in, out, nx, ny, nsig, tw, s);
     case 32: return x_ty<FWD, R, 32>(ty, in, out, nx, ny, nsig, tw, s);
     case 64: return x_ty<FWD, R, 64>(ty, in, out, nx, ny, nsig, tw, s);
     case 128: return x_ty<FWD, R, 128>(ty, in, out, nx, ny, nsig, tw, s);
-    case 256:
-        if (wide && ty != 4) return x_ty<FWD, R, 256, 16>(ty, in, out, nx, ny, nsig, tw, s);
-        return x_ty<FWD, R, 256>(ty, in, out, nx, ny, nsig, tw, s);
+    case 256: return x_ty<FWD, R, 256>(ty, in, out, nx, ny, nsig, tw, s);
     case 512: return x_ty<FWD, R, 512>(ty, in, out, nx, ny, nsig, tw, s);
     case 1024: return x_ty<FWD, R, 1024>(ty, in, out, nx, ny, nsig, tw, s);
     case 2048: return x_ty<FWD, R, 2048>(ty, in, out, nx, ny, nsig, tw, s);
@@ -124,19 +118,18 @@ bool x_tile_supported(bool fp64, int LX, int ty)
     if (ty == 0) return true;
     if (ty != 4 && ty != 8 && ty != 12 && ty != 16 && ty != 24 && ty != 32) return false;
     const int M = LX / 2;
-    const int V = x_vals(M), GT = M / V;
     const size_t lds = (fp64 ? 16 : 8) * (size_t)ty * (size_t)(fft_region(M) | 1);
-    return GT * ty <= 1024 && GT * ty >= 64 && lds <= 163840;
+    auto ok = [&](int V) { return M / V * ty <= 1024 && M / V * ty >= 64 && lds <= 163840; };
+    // (a tile serves both directions)
+    return fp64 ? ok(x_vals<double, true>(M)) && ok(x_vals<double, false>(M))
+                : ok(x_vals<float, true>(M)) && ok(x_vals<float, false>(M));
 }
 
 hipError_t launch_xfwd(bool fp64, int LX, const void* in, void* out, int nx, int ny, int nsig,
-                       const void* twx, hipStream_t s, int ty, bool for_gradient)
+                       const void* twx, hipStream_t s, int ty)
 {
-    // FP32 spectra of the thickness gradient in their own order of operations (see x_vals)
-    if (!fp64 && for_gradient && LX == 512)
-        return x_ty<true, float, 512, fft_vals(256)>(ty, in, out, nx, ny, nsig, twx, s);
     if (fp64) return x_lx<true, double>(LX, ty, in, out, nx, ny, nsig, twx, s);
-    return x_lx<true, float>(LX, ty, in, out, nx, ny, nsig, twx, s, for_gradient);
+    return x_lx<true, float>(LX, ty, in, out, nx, ny, nsig, twx, s);
 }
 
 hipError_t launch_xinv(bool fp64, int LX, const void* in, void* out, int nx, int ny, int nsig,

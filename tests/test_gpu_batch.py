@@ -1,0 +1,71 @@
+"""A state's field and gradients do not depend on the batch it is in, on the states
+of a run, or on which of its gradients are asked for: bit for bit, on both sides of
+every size rule that follows the number of states (tiles of the x passes, threads of
+the fused kernels, blocks per tile of the mixing kernel, waves per tile of the
+thickness gradient)."""
+import numpy as np
+import pytest
+
+from paper_1910_07054_amd import hfd
+
+pytestmark = pytest.mark.gpu
+
+F, D, EQ = hfd.HFD_FP32, hfd.HFD_FP64, hfd.HFD_EQUIDISTANT
+
+
+@pytest.fixture(scope="module", autouse=True)
+def _gpu():
+    torch = pytest.importorskip("torch")
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    hfd.load()
+
+
+def _setup(nx, ny, nz, B, flags):
+    import torch
+    rng = np.random.default_rng(100 * nx + nz)
+    t = np.full(nz, 1.25) if flags & EQ else rng.uniform(1.0, 3.0, nz)
+    gap = 0.0 if flags & EQ else 0.2
+    z = np.concatenate([[0.0], np.cumsum(t + gap)[:-1]])
+    plan = hfd.Plan(nx, ny, 2.0, 2.0, t, z, batch_max=B, flags=flags)
+    dt = torch.float64 if flags & D else torch.float32
+    m, g = (torch.from_numpy(rng.standard_normal((B, 3, nz, ny, nx))).to(dt).cuda() for _ in range(2))
+    return plan, m, g
+
+
+FIELDS = [
+    (100, 60, 4, 12, F), (100, 60, 4, 12, D), (70, 25, 3, 128, F), (100, 60, 8, 12, EQ | D),  # rows of 65 to 128 cells
+    (200, 20, 3, 40, F), (200, 20, 3, 40, D),       # rows of 129 to 256
+    (40, 100, 4, 32, F), (30, 30, 12, 32, F), (30, 30, 4, 64, D), (30, 260, 6, 8, F), (300, 600, 2, 6, F),
+    (33, 20, 14, 40, F), (33, 20, 14, 40, D), (64, 300, 13, 6, F), (9, 9, 40, 64, F), (64, 64, 24, 8, EQ),
+]
+
+
+@pytest.mark.parametrize("case", FIELDS, ids=lambda c: "x".join(map(str, c)))
+def test_field_of_a_state_does_not_depend_on_its_batch(case):
+    import torch
+    plan, m, _ = _setup(*case)
+    B = case[3]
+    h = plan.field(m)
+    for b in (0, B // 2, B - 1):
+        assert torch.equal(plan.field(m[b:b + 1].clone())[0], h[b]), b
+    assert torch.equal(plan.field(m[:B // 2].clone()), h[:B // 2])
+    if plan.info().fused:
+        plan.set_fused(B, chunk=B // 2)
+        assert torch.equal(plan.field(m), h)
+    plan.destroy()
+
+
+GRADIENTS = [(100, 60, 4, 12, F), (200, 75, 6, 4, F), (256, 256, 6, 16, F), (100, 60, 14, 12, F), (128, 128, 4, 4, D)]
+
+
+@pytest.mark.parametrize("case", GRADIENTS, ids=lambda c: "x".join(map(str, c)))
+def test_gradient_in_m_of_a_state(case):
+    import torch
+    plan, m, g = _setup(*case)
+    B = case[3]
+    gm, _ = plan.vjp(m, g)
+    assert torch.equal(plan.vjp(m, g, want_t=False)[0], gm)
+    for b in (0, B - 1):
+        assert torch.equal(plan.vjp(m[b:b + 1].clone(), g[b:b + 1].clone())[0][0], gm[b]), b
+    plan.destroy()
