@@ -100,8 +100,10 @@ struct alignas(4 * sizeof(R)) MG {
 // block's waves (1, 2 or 4), which take groups of QC source positions and of QC
 // layers in turn: a group's spectra stay in registers (FP64) while the wave
 // walks the positions above them, or the layers up to them, with the next one's
-// D or S entries in flight.  Each wave keeps its own per-position sums in LDS,
-// added up over waves and lanes at the end in a fixed order.
+// D or S entries in flight.  The groups are dealt to `shares` (4, or 2 where 4 do not
+// fit in LDS), each with per-position sums of its own in LDS, added up over shares and
+// lanes at the end in a fixed order; a wave takes one share (ONE) or several, one after
+// the other, so that the result does not depend on the waves per block.
 // Block order: groups of 8 tiles, within a group every state of the launch,
 // with the 8 tiles on consecutive block indices: the states of one tile are 8
 // indices apart, so they run one after the other on one XCD and read that
@@ -116,12 +118,12 @@ struct alignas(4 * sizeof(R)) MG {
 // itab per geometry: see itab_layout.  D per geometry: [QX][nzt][6][QY], nzt D slots per row.
 // lp per geometry: 1/t_l, then the trace term of the diagonal blocks.
 // partial[b][2nz][tile]: the tile's position gradients.
-template <typename R>
+template <typename R, bool ONE>
 __global__ __launch_bounds__(256, 2) void k_tgrad(
     const cpx<R>* __restrict__ Mh, const cpx<R>* __restrict__ Gh, int nz, int M, int LY,
     const R* __restrict__ Q, long long qcs, const int* __restrict__ qslot, const R* __restrict__ D, int nzt,
     const int* __restrict__ itab, int itab_stride, const R* __restrict__ lp, int bpg, int QY, int b0, int nst,
-    int ntiles, double* __restrict__ partial)
+    int ntiles, int nshare, double* __restrict__ partial)
 {
     constexpr int QC = 3;
     const int L = blockIdx.x, r8 = L >> 3;
@@ -136,7 +138,7 @@ __global__ __launch_bounds__(256, 2) void k_tgrad(
     const int half = LY >> 1, tpk = (half + 31) >> 5;
     const int kx = __builtin_amdgcn_readfirstlane(tile / tpk), kyb = tile - kx * tpk;
     const int lane = threadIdx.x & 63, W = blockDim.x >> 6;
-    const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), shares = ONE ? W : nshare;
     const int t0 = kyb * 32 + (lane & 31), p2 = lane >> 5;
     const bool active = t0 < half;
     const int t = active ? t0 : 0;
@@ -167,10 +169,10 @@ __global__ __launch_bounds__(256, 2) void k_tgrad(
                              (unsigned)((packed ? 2 : 1) * qcs * sizeof(R)));
 
     extern __shared__ __align__(16) unsigned char smem_raw[];
-    double* accw = reinterpret_cast<double*>(smem_raw) + (size_t)w * NI * 64 + lane;  // [W][NI][64]
+    double* acc0 = reinterpret_cast<double*>(smem_raw) + lane;  // [shares][NI][64]
     // (M, G) of component c, layer l: [nz][3][64]
-    MG<R>* sm = reinterpret_cast<MG<R>*>(smem_raw + sizeof(double) * 64 * (size_t)W * NI) + lane;
-    for (int v = 0; v < NI; ++v) accw[v * 64] = 0.0;
+    MG<R>* sm = reinterpret_cast<MG<R>*>(smem_raw + sizeof(double) * 64 * (size_t)shares * NI) + lane;
+    for (int v = w; v < shares * NI; v += W) acc0[v * 64] = 0.0;
 
     const bool rowM = packed && ((p2 == 1 && t != 0) || mirror);
     const unsigned vd = (unsigned)(kq + (rowM ? drow : 0LL)), vq = (unsigned)(kq + (rowM ? qcs : 0LL));
@@ -273,10 +275,14 @@ __global__ __launch_bounds__(256, 2) void k_tgrad(
             }
         };
         // groups u = 0, 1, .. of source positions from the lowest and of layers from the
-        // highest, both by falling cost, dealt to the waves in turn and back
+        // highest, both by falling cost, dealt to the shares in turn and back
         const int ni = (NI + QC - 1) / QC, nl = (nz + QC - 1) / QC;
-        for (int r = 0; r * W < 2 * (ni > nl ? ni : nl); ++r) {
-            const int e = r * W + ((r & 1) ? W - 1 - w : w), u = e >> 1;
+        for (int q = 0; q == 0 || (!ONE && q * W < shares); ++q)
+        for (int r = 0; r * shares < 2 * (ni > nl ? ni : nl); ++r) {
+            // this wave's share (two of four: w and 3 - w, which even out)
+            const int h = (q & 1) ? (q + 1) * W - 1 - w : q * W + w;
+            double* accw = acc0 + (size_t)h * NI * 64;
+            const int e = r * shares + ((r & 1) ? shares - 1 - h : h), u = e >> 1;
             if ((e & 1) == 0) {
                 if (u >= ni) continue;
                 // source positions q0 .. q0 + QC - 1 against the positions above them
@@ -400,10 +406,9 @@ __global__ __launch_bounds__(256, 2) void k_tgrad(
     else sweep(std::false_type{});
     __syncthreads();
     double* out = partial + (long long)b * 2 * nz * ntiles + slot;
-    const double* acc0 = reinterpret_cast<const double*>(smem_raw) + lane;
     for (int v = w; v < NI; v += W) {
         double sv = 0.0;
-        for (int k = 0; k < W; ++k) sv += acc0[(size_t)(k * NI + v) * 64];
+        for (int k = 0; k < shares; ++k) sv += acc0[(size_t)(k * NI + v) * 64];
         sv = wave_sum(sv * weight);
         if (lane == 0) out[(long long)v * ntiles] = sv;
     }
@@ -741,25 +746,36 @@ int tgrad_tiles(int M, int LY)
     return M * ((LY / 2 + 31) / 32) + 1;
 }
 
-// LDS of k_tgrad: the sums of its waves and the staged spectra of M and G
+// LDS of k_tgrad: the sums of its shares and the staged spectra of M and G
 template <typename R>
-static size_t tgrad_lds(int waves, int nz, int ni)
+static size_t tgrad_lds(int shares, int nz, int ni)
 {
-    return sizeof(double) * 64 * (size_t)waves * ni + sizeof(MG<R>) * 64 * 3 * (size_t)nz;
+    return sizeof(double) * 64 * (size_t)shares * ni + sizeof(MG<R>) * 64 * 3 * (size_t)nz;
 }
 
-// Waves per tile: 4 where they fit, else 2, else one wave per tile without staging
-// (which takes 3.2 and 3.5 times as long at 64 x 64 x 24 and 32 in FP32, 4.7 at 18 in FP64).
-// Up to 4 layers have too few groups of positions and layers for 4 waves, up to 8
-// too few where blocks queue up anyway: whole calls with 1, 2 and 4 waves take
-//   250 x 250 x 2, 16 stacks 267, 304, 448 us     60 x 60 x 2, 1 stack 29, 26, 25
-//   128 x 128 x 4, 4 stacks   76,  64,  72        128 x 128 x 4, 1 stack 49, 38, 41
-//   250 x 250 x 5, 16 stacks 878, 919, 1049       128 x 128 x 5, 1 stack 81, 59, 54
-//   200 x 200 x 8, 16 stacks 1672 (2), 1755 (4)   256 x 256 x 9, 2 stacks 218 (2), 209 (4)
-//   256 x 256 x 10, 16 stacks 1777 (2), 1580 (4)
+// Shares of a tile's groups (see k_tgrad), by the plan alone: 4 where their sums fit in
+// LDS, else 2, else none (0): one wave per tile without staging, which takes 3.2 and 3.5
+// times as long at 64 x 64 x 24 and 32 in FP32, 4.7 at 18 in FP64.  Up to 3 layers have too
+// few groups for 4.
+template <typename R>
+static int tgrad_shares(int nz, int ni_max)
+{
+    constexpr size_t kMax = 163840;
+    if (nz > 3 && tgrad_lds<R>(4, nz, ni_max) <= kMax) return 4;
+    return tgrad_lds<R>(2, nz, ni_max) <= kMax ? 2 : 0;
+}
+
+// Waves per tile, at most one per share: fewer where blocks queue up anyway.  A wave
+// with several shares pays for their sums, and from 6 layers on for the blocks that
+// their LDS keeps off a CU.  Whole calls with 1, 2 and 4 waves, a share each, and with 4
+// shares on 2 waves:
+//   250 x 250 x 3, 16 states  361, 403, 563 (2 shares on 1 wave: 370)   60 x 60 x 3  35, 27, 26
+//   128 x 128 x 4, 4 states    74,  64,  71,   65                       60 x 60 x 4  43, 32, 29
+//   250 x 250 x 5, 16 states  614, 637, 808,  667                      128 x 128 x 5 55, 42, 43
+//   250 x 250 x 8, 16 states 1383, 1116, 1185, 1391                     60 x 60 x 8  77, 52, 38
 static int tgrad_waves(int nz, unsigned nblk)
 {
-    if (nblk >= 4096) return nz <= 2 ? 1 : nz <= 8 ? 2 : 4;
+    if (nblk >= 4096) return nz <= 3 ? 1 : nz <= 5 ? 2 : 4;
     return nz <= 4 && nblk >= 512 ? 2 : 4;
 }
 
@@ -769,17 +785,16 @@ static hipError_t tgrad_r(const void* Mh, const void* Gh, int nz, int M, int LY,
                           int itab_stride, int ni_max, const void* lp, int bpg, int QY, int ntiles, unsigned nblk,
                           double* partial, hipStream_t s)
 {
-    constexpr size_t kMax = 163840;
-    int waves = tgrad_waves(nz, nblk);
-    if (tgrad_lds<R>(waves, nz, ni_max) > kMax) waves = tgrad_lds<R>(2, nz, ni_max) <= kMax ? 2 : 0;
-    if (!derivative_rows_fit(2, nzt, QY, sizeof(R))) waves = 0;
-    if (waves > 0) {
-        const size_t lds = tgrad_lds<R>(waves, nz, ni_max);
-        const hipError_t e = ensure_lds_limit((const void*)k_tgrad<R>, lds > 65536 ? (int)kMax : 0);
+    const int shares = derivative_rows_fit(2, nzt, QY, sizeof(R)) ? tgrad_shares<R>(nz, ni_max) : 0;
+    if (shares > 0) {
+        const int waves = std::min(tgrad_waves(nz, nblk), shares);
+        const auto kernel = waves == shares ? k_tgrad<R, true> : k_tgrad<R, false>;
+        const size_t lds = tgrad_lds<R>(shares, nz, ni_max);
+        const hipError_t e = ensure_lds_limit((const void*)kernel, lds > 65536 ? 163840 : 0);
         if (e != hipSuccess) return e;
-        hipLaunchKernelGGL(k_tgrad<R>, dim3(nblk), dim3(64 * waves), lds, s, (const cpx<R>*)Mh,
+        hipLaunchKernelGGL(kernel, dim3(nblk), dim3(64 * waves), lds, s, (const cpx<R>*)Mh,
                            (const cpx<R>*)Gh, nz, M, LY, (const R*)Q, qcs, qslot, (const R*)D, nzt, itab,
-                           itab_stride, (const R*)lp, bpg, QY, b0, nb, ntiles, partial);
+                           itab_stride, (const R*)lp, bpg, QY, b0, nb, ntiles, shares, partial);
     } else {
         const size_t lds = sizeof(double) * 64 * (size_t)ni_max;
         hipLaunchKernelGGL((k_tgrad_rows<R, 4>), dim3(nblk), dim3(64), lds, s, (const cpx<R>*)Mh,

@@ -69,3 +69,22 @@ def test_gradient_in_m_of_a_state(case):
     for b in (0, B - 1):
         assert torch.equal(plan.vjp(m[b:b + 1].clone(), g[b:b + 1].clone())[0][0], gm[b]), b
     plan.destroy()
+
+
+# one state in few blocks, many in many: the waves per tile change between them (at
+# 576 and at 4320 blocks of 33 x 3 cells), at 1 to 3 layers, 4 and 5, and more; 24
+# layers with gaps are the two-share form
+THICKNESS = [(33, 3, 1, 60, F), (33, 3, 2, 60, F), (33, 3, 3, 60, F), (33, 3, 4, 8, F), (33, 3, 4, 60, F),
+             (33, 3, 5, 60, F), (33, 3, 6, 60, F), (33, 3, 8, 60, F), (33, 3, 24, 60, F), (33, 3, 3, 60, D),
+             (33, 3, 5, 60, D), (33, 3, 17, 60, D), (200, 75, 6, 4, F), (100, 60, 4, 12, F)]
+
+
+@pytest.mark.parametrize("case", THICKNESS, ids=lambda c: "x".join(map(str, c)))
+def test_thickness_gradient_of_a_state(case):
+    import torch
+    plan, m, g = _setup(*case)
+    B = case[3]
+    gt = plan.vjp(m, g, want_m=False)[1]
+    for b in (0, B // 2, B - 1):
+        assert torch.equal(plan.vjp(m[b:b + 1].clone(), g[b:b + 1].clone(), want_m=False)[1][0], gt[b]), b
+    plan.destroy()
