@@ -920,6 +920,14 @@ struct YPassShape {
     static constexpr int NGL = (int)(65536 / (sizeof(cpx<R>) * fft_region(LY)));
     static constexpr int NG = NG0 < NGL ? NG0 : (NGL < 1 ? 1 : NGL);
     static constexpr int NT = NG * GT;
+    // whether the groups of k_yfwd walk over columns: not in FP64 from 2048 points on,
+    // where kept twiddles leave no registers for the next column (4096 points: 172
+    // registers spilled instead of 106) and a block is one group, so that two columns each
+    // make a long last round.  Walking, 2304 columns of 2048 cells took 139 us instead of 117,
+    // 6144 of 1025 283 instead of 278, 2304 of 1000 (2048 points) 35.7 instead of 32.3.
+    // k_yinv, which stores half of a transform, gains with many columns: 275 us
+    // instead of 354 for the 6144.
+    static constexpr bool WALK_FWD = sizeof(R) == 4 || LY < 2048;
 };
 
 // Columns of n_in <= LY/2 complex values (zero padded to LY: the first radix pass
@@ -940,19 +948,30 @@ __global__ __launch_bounds__((YPassShape<R, LY>::NT)) void k_yfwd(const cpx<R>* 
     using S = YPassShape<R, LY>;
     __shared__ cpx<R> sh[S::NG * fft_region(LY)];
     const int tid = threadIdx.x, grp = tid / S::GT, g = tid % S::GT;
-    const long long step = (long long)gridDim.x * S::NG;
-    Twiddles<R, LY> tw;
-    tw.load(g, twy, 1);
-    for (long long c = (long long)blockIdx.x * S::NG + grp; c < ncols; c += step) {
-        const cpx<R>* src = in + c * n_in;
-        cpx<R>* dst = out + c * LY;
-        cpx<R> v[S::V];
-        fft_first_loads<R, LY, true>(v, g, [&](int pos) -> cpx<R> {
-            return pos < n_in ? src[pos] : cpx<R>{R(0), R(0)};
-        });
-        wave_fft_pre<R, LY, false, true>(sh + grp * fft_region(LY), g, tw, v,
-                                         [&](int pos, cpx<R> z) { dst[pos] = z; });
-        wave_sync();
+    const long long c0 = (long long)blockIdx.x * S::NG + grp;
+    if constexpr (!S::WALK_FWD) {
+        if (c0 >= ncols) return;
+        const cpx<R>* src = in + c0 * n_in;
+        cpx<R>* dst = out + c0 * LY;
+        wave_fft<R, LY, false, true>(
+            sh + grp * fft_region(LY), g, twy, 1,
+            [&](int pos) -> cpx<R> { return pos < n_in ? src[pos] : cpx<R>{R(0), R(0)}; },
+            [&](int pos, cpx<R> z) { dst[pos] = z; });
+    } else {
+        const long long step = (long long)gridDim.x * S::NG;
+        Twiddles<R, LY> tw;
+        tw.load(g, twy, 1);
+        for (long long c = c0; c < ncols; c += step) {
+            const cpx<R>* src = in + c * n_in;
+            cpx<R>* dst = out + c * LY;
+            cpx<R> v[S::V];
+            fft_first_loads<R, LY, true>(v, g, [&](int pos) -> cpx<R> {
+                return pos < n_in ? src[pos] : cpx<R>{R(0), R(0)};
+            });
+            wave_fft_pre<R, LY, false, true>(sh + grp * fft_region(LY), g, tw, v,
+                                             [&](int pos, cpx<R> z) { dst[pos] = z; });
+            wave_sync();
+        }
     }
 }
 

@@ -9,11 +9,11 @@ namespace hfd {
 // blocks against 2048 took 9.4 and 10.6 us at 256 x 256 x 8, 44 and 48 us at
 // 1024 x 1024 x 3, 139 and 134 us at 16 states of 256 x 256 x 10.
 template <typename R, int LY>
-static unsigned y_blocks(long long ncols)
+static unsigned y_blocks(long long ncols, bool walk)
 {
     const long long need = (ncols + YPassShape<R, LY>::NG - 1) / YPassShape<R, LY>::NG;
     const long long some = need / 2 < 1024 ? 1024 : need / 2 > 2048 ? 2048 : need / 2;
-    return (unsigned)(need < some ? need : some);
+    return (unsigned)(!walk || need < some ? need : some);
 }
 
 template <typename R, int LY>
@@ -21,7 +21,9 @@ static hipError_t yfwd_t(const void* in, void* out, int n, long long ncols, cons
                          hipStream_t s)
 {
     if (2 * n > LY || ncols < 1) return ncols < 1 ? hipSuccess : hipErrorInvalidValue;
-    hipLaunchKernelGGL((k_yfwd<R, LY>), dim3(y_blocks<R, LY>(ncols)), dim3(YPassShape<R, LY>::NT), 0, s,
+    const bool walk = YPassShape<R, LY>::WALK_FWD;
+    if (!walk && ncols > 0x7fffffffLL) return hipErrorInvalidValue;
+    hipLaunchKernelGGL((k_yfwd<R, LY>), dim3(y_blocks<R, LY>(ncols, walk)), dim3(YPassShape<R, LY>::NT), 0, s,
                        (const cpx<R>*)in, (cpx<R>*)out, n, ncols, (const cpx<R>*)tw);
     return hipGetLastError();
 }
@@ -31,7 +33,7 @@ static hipError_t yinv_t(const void* in, void* out, int n, long long ncols, cons
                          hipStream_t s)
 {
     if (2 * n > LY || ncols < 1) return ncols < 1 ? hipSuccess : hipErrorInvalidValue;
-    hipLaunchKernelGGL((k_yinv<R, LY>), dim3(y_blocks<R, LY>(ncols)), dim3(YPassShape<R, LY>::NT), 0, s,
+    hipLaunchKernelGGL((k_yinv<R, LY>), dim3(y_blocks<R, LY>(ncols, true)), dim3(YPassShape<R, LY>::NT), 0, s,
                        (const cpx<R>*)in, (cpx<R>*)out, n, ncols, (const cpx<R>*)tw);
     return hipGetLastError();
 }

@@ -155,3 +155,24 @@ def test_x_passes_of_128_points_many_rows(nx, ny, nz, B, fp64):
                 refs[b] = oracle.field(nx, ny, wl.dx, wl.dy, wl.z_bottom[0], wl.thickness[0], mused[b])
             assert rel_err(h[b], refs[b]) < (1e-10 if fp64 else 1e-5), (ty, b)
     plan.destroy()
+
+
+# 4096-point column transforms, more columns than blocks: one column per group in the
+# FP64 forward pass, walking groups in the others
+@pytest.mark.parametrize("fp64", [False, True], ids=["fp32", "fp64"])
+@pytest.mark.parametrize("nx,ny,nz,B", [(5, 1025, 2, 43), (3, 2048, 1, 86), (1, 1300, 1, 1)])
+def test_y_transforms_of_4096_points(nx, ny, nz, B, fp64):
+    wl = W.small_case(nx, ny, nz, seed=2200 + ny, batch=1)
+    m = np.stack([np.roll(wl.m[0], 7 * b, axis=-2) for b in range(B)])
+    plan = hfd.Plan(nx, ny, wl.dx, wl.dy, wl.thickness[0], wl.z_bottom[0], batch_max=B,
+                    flags=hfd.HFD_FP64 if fp64 else hfd.HFD_FP32)
+    h, mused = run_field(plan, m)
+    plan.destroy()
+    rng = np.random.default_rng(ny)
+    smp = np.stack([rng.integers(0, nz, 30), rng.integers(0, ny, 30), rng.integers(0, nx, 30)], axis=1)
+    smp[0], smp[1] = (0, 0, 0), (nz - 1, ny - 1, nx - 1)
+    for b in (0, B // 2, B - 1):
+        ref = oracle.field(nx, ny, wl.dx, wl.dy, wl.z_bottom[0], wl.thickness[0], mused[b], samples=smp)
+        got = h[b][:, smp[:, 0], smp[:, 1], smp[:, 2]].T
+        err = np.abs(got - ref).max() / np.linalg.norm(ref, axis=1).max()
+        assert err < (1e-10 if fp64 else 1e-5), (b, err)
