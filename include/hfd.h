@@ -114,7 +114,7 @@ enum {
  * one stack or in several, is computed and stored once (hfd_info.tensor_slots
  * counts them): thickness candidates that differ in one layer share the
  * tensors of all other pairs.  Memory is reserved for n_geom * nz (nz + 1) / 2
- * pair tensors, so hfd_set_thickness never reallocates it; a kx row of that
+ * pair tensors, so hfd_set_thickness never reallocates it; two kx rows of that
  * table must stay below 2 GiB (else HFD_ENOTSUP).
  */
 hfd_status hfd_setup_tensor(hfd_plan *out, int nx, int ny, double dx, double dy, int nz,
@@ -129,7 +129,8 @@ hfd_status hfd_setup_tensor(hfd_plan *out, int nx, int ny, double dx, double dy,
  * geometry changes, the lateral grid stays.  Blocks until the new tensor is
  * ready on `stream`; allocates nothing (the setup scratch belongs to the
  * plan) except that the thickness-derivative tables grow when the new
- * geometry has more distinct interface offsets than any earlier one.
+ * geometry has more distinct interface offsets, or more tables of them, than
+ * any earlier one.
  *
  * The stored Fourier tensor is rewritten in place, so a HIP graph that
  * captured hfd_demag_field (or hfd_demag_vjp without grad_thickness) stays
@@ -149,6 +150,9 @@ hfd_status hfd_set_thickness(hfd_plan plan, const double *thickness, const doubl
  * h = -N * m  for `batch` states (Sec. 3.1, hybrid 2D FFT + explicit z sum).
  * m and h: device [batch][3][nz][ny][nx]; h is overwritten.  batch must be in
  * [1, batch_max] and a multiple of n_geom.  m == h (or overlap) -> HFD_EINVAL.
+ * On one path (hfd_set_path; hfd_autotune may choose another per batch) a
+ * state's result does not depend on the batch it is in, bit for bit; neither do
+ * the gradients of hfd_demag_vjp.
  */
 hfd_status hfd_demag_field(hfd_plan plan, const void *m, void *h, int batch, void *stream);
 

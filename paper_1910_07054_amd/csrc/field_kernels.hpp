@@ -81,7 +81,9 @@ struct XPassShape {
     static_assert(TY % RPG == 0 && NT % TY == 0 && KI * KS == M / 2, "x pass tile");
 };
 
-// n / d for n < 2^32 by a multiplication (d >= 1; make(d) on the host):
+// n / d for n < 2^32 by a multiplication (d >= 1; make(d) on the host), the unsigned
+// form of T. Granlund and P. L. Montgomery, "Division by invariant integers using
+// multiplication", PLDI 1994:
 // q = (t + (n - t) / 2) >> (l - 1), t = mulhi(n, m), m = 2^32 (2^l - d) / d + 1,
 // l = ceil(log2 d)
 struct FastDiv {
@@ -140,9 +142,11 @@ __device__ __forceinline__ void real_split_inv(cpx<R>& a, cpx<R>& b, cpx<R> w, b
 // large ones.  All global accesses of a thread are requested together, and
 // the indices are divided out once per thread; with the split in the rows (one
 // more LDS round trip) and an index division per element the two passes of
-// 64 states of 512 x 512 x 4 took 932 + 1360 us, now 620 + 567 (2.4 GB each at
-// 4.2 TB/s; a copy runs at 4.9), those of one 256 x 256 x 8 state 9.1 + 8.7,
-// now 6.6 + 6.2.
+// 64 states of 512 x 512 x 4 took 932 + 1360 us, now 630 + 565 (2.4 GB each at
+// 3.8 and 4.3 TB/s; a copy runs at 4.9), those of one 256 x 256 x 8 state 9.1 + 8.7,
+// now 6.8 + 5.4.  (With the exchange layout of FP64, pos + pos/8, in FP32 too that
+// forward pass takes 573 us and no other size gains: it waits for its stores, which
+// meet differently.)
 // ---------------------------------------------------------------------------
 template <typename R, int LX, int TYO = 0, int XV = x_vals<R, true>(LX / 2)>
 __global__ __launch_bounds__((XPassShape<R, LX, TYO, XV>::NT), (XPassShape<R, LX, TYO, XV>::WPE)) void k_xfwd(

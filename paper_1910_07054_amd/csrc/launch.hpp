@@ -124,7 +124,7 @@ int tgrad_tiles(int M, int LY);
 // of layer r-1 is there + 2 if the bottom of layer r is there); pos_bot[nz],
 // pos_top[nz]; zpq[nsp][nsp] at `zpq`: 2 x (D slot of |z_p - z_q|) + 1 when
 // z_p < z_q.  nsp = 2nz rounded up to 8 and every row 32-byte aligned, so a
-// chunk of 8 entries is two aligned 16-byte loads; padding entries are slot 0.
+// chunk of 4 entries is one aligned 16-byte load; padding entries are slot 0.
 struct ITabLayout {
     int nsp, info, pbot, ptop, zpq, stride;
 };

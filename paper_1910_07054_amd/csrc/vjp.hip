@@ -414,16 +414,14 @@ __global__ __launch_bounds__(256, 2) void k_tgrad(
     }
 }
 
-// QC (4 or 8) consecutive table entries from a 4 QC-byte aligned address
-template <int QC>
-__device__ inline void load_chunk(const int* __restrict__ src, int (&dst)[QC])
+// four consecutive table entries from a 16-byte aligned address
+__device__ inline void load_chunk(const int* __restrict__ src, int (&dst)[4])
 {
-    static_assert(QC == 4 || QC == 8, "interface chunks hold 4 or 8 positions");
-#pragma unroll
-    for (int h = 0; h < QC / 4; ++h) {
-        const int4 a = reinterpret_cast<const int4*>(src)[h];
-        dst[4 * h] = a.x; dst[4 * h + 1] = a.y; dst[4 * h + 2] = a.z; dst[4 * h + 3] = a.w;
-    }
+    const int4 a = *reinterpret_cast<const int4*>(src);
+    dst[0] = a.x;
+    dst[1] = a.y;
+    dst[2] = a.z;
+    dst[3] = a.w;
 }
 
 // Stacks whose spectra do not fit in LDS: per-position gradient sums of one wave
