@@ -917,7 +917,7 @@ hfd_status run_field(hfd_plan p, const void* in, void* out, int batch, int adjoi
             char* out_c = (char*)out + (size_t)b0 * state;
             const int* qs_c = p->qslot + (size_t)g0 * p->P;
             const char* lp_c = (const char*)p->lp + (size_t)g0 * 2 * p->nz * p->rsz;
-            HFD_HIP(launch_xfwd(p->fp64, p->Lx, in_c, x1, p->nx, p->ny, chunk * S, p->twx, s, xty));
+            HFD_HIP(launch_xfwd(p->fp64, p->Lx, in_c, x1, p->nx, p->ny, chunk * S, p->twx, s, xty, adjoint != 0));
             HFD_HIP(launch_fused(p->fp64, p->Ly, p->nz, x1, p->ny, p->M, chunk, p->Q, p->qcs, qs_c,
                                  p->QX, p->QY, lp_c, bpg_c, adjoint, p->twy, s,
                                  gen));
@@ -934,7 +934,7 @@ hfd_status run_field(hfd_plan p, const void* in, void* out, int batch, int adjoi
     };
     auto on = [&]() { return only < 0 || only == k; };
     if (on())
-        HFD_HIP(launch_xfwd(p->fp64, p->Lx, in, x1, p->nx, p->ny, nsig, p->twx, s, xty));
+        HFD_HIP(launch_xfwd(p->fp64, p->Lx, in, x1, p->nx, p->ny, nsig, p->twx, s, xty, adjoint != 0));
     mark();
     if (path == 0) {
         if (on())
@@ -1198,7 +1198,7 @@ static hfd_status adjoint_and_spectra(hfd_plan p, const void* gh, void* gm, int 
         const char* in_c = (const char*)gh + (size_t)b0 * state;
         char* out_c = (char*)gm + (size_t)b0 * state;
         const char* lp_c = (const char*)p->lp + (size_t)g0 * 2 * p->nz * p->rsz;
-        HFD_HIP(launch_xfwd(p->fp64, p->Lx, in_c, p->X1, p->nx, p->ny, chunk * S, p->twx, s, xty));
+        HFD_HIP(launch_xfwd(p->fp64, p->Lx, in_c, p->X1, p->nx, p->ny, chunk * S, p->twx, s, xty, true));
         HFD_HIP(launch_yfwd(p->fp64, p->Ly, p->X1, (char*)p->Hh + (size_t)b0 * hstate, p->ny,
                             (long long)chunk * S * p->M, p->twy, s));
         HFD_HIP(launch_fused(p->fp64, p->Ly, p->nz, p->X1, p->ny, p->M, chunk, p->Q, p->qcs,
@@ -1236,10 +1236,11 @@ hfd_status hfd_demag_vjp(hfd_plan p, const void* m, const void* grad_h, void* gr
     } else {
         // (the five-pass paths use Mh and Hh themselves: grad_m first)
         if (grad_m) HFD_TRY(run_field(p, grad_h, grad_m, batch, 1, s));
-        HFD_HIP(launch_xfwd(p->fp64, p->Lx, grad_h, p->X1, p->nx, p->ny, nsig, p->twx, s, xty_for(p, batch)));
+        HFD_HIP(launch_xfwd(p->fp64, p->Lx, grad_h, p->X1, p->nx, p->ny, nsig, p->twx, s, xty_for(p, batch),
+                            true));
         HFD_HIP(launch_yfwd(p->fp64, p->Ly, p->X1, p->Hh, p->ny, ncols, p->twy, s));
     }
-    HFD_HIP(launch_xfwd(p->fp64, p->Lx, m, p->X1, p->nx, p->ny, nsig, p->twx, s, xty_for(p, batch)));
+    HFD_HIP(launch_xfwd(p->fp64, p->Lx, m, p->X1, p->nx, p->ny, nsig, p->twx, s, xty_for(p, batch), true));
     HFD_HIP(launch_yfwd(p->fp64, p->Ly, p->X1, p->Mh, p->ny, ncols, p->twy, s));
     const int bpg = batch / p->G;
     const bool stored = (p->flags & HFD_STORE_DTENSOR) != 0;

@@ -24,23 +24,22 @@
 
 namespace hfd {
 
-// Values per lane of the x passes' transforms, one choice per length, precision and
-// direction: the order of a transform's roundings follows from it, and a state's
-// results depend neither on the batch it is in nor on which of its gradients are
-// asked for.  256 points (rows of 129 to 256 cells) take 16 in inverse passes and in
-// FP64: two radix-16 passes with one exchange instead of 8 8 4 with two, and half the
-// threads per row.  At equal tile heights, 8 and 16 values: 256 x 256 x 8 (24 rows) forward
-// 6.8, 6.3 us, inverse 6.1, 5.4, FP64 (8 rows) 9.7, 8.9 and 8.2, 7.1; 32 layers (32 rows)
-// 18.6, 16.7 and 19.4, 18.2; 16 states of 10 layers (32 rows) 94, 91 and 78, 79.  FP32
-// forward passes stay at 8: one kernel makes the spectra of the field, of its transpose
-// and of the thickness gradient, whose FP64 values stay what they were (16 are no more
-// accurate, and move its seventh digit).  At 128 points 16 values are slower below 8192 rows
-// (128 x 128 x 8: 3.3 + 3.2 us against 3.7 + 3.5) and a little faster above (8 states: 9.5 + 8.3
-// against 8.7 + 8.3), so 8 for all.
-template <typename R, bool FWD>
-__host__ __device__ constexpr int x_vals(int M)
+// Values per lane of the x passes' transforms, one choice per length, precision and call:
+// the order of a transform's roundings follows from it, and a state's results depend
+// neither on the batch it is in nor on which of its gradients are asked for.  256 points
+// (rows of 129 to 256 cells) take 16: two radix-16 passes with one exchange instead of
+// 8 8 4 with two, and half the threads per row.  At equal tile heights, 8 and 16 values:
+// 256 x 256 x 8 (24 rows) forward 6.8, 6.3 us, inverse 6.1, 5.4, FP64 (8 rows) 9.7, 8.9 and
+// 8.2, 7.1; 32 layers (32 rows) 18.6, 16.7 and 19.4, 18.2; 16 states of 10 layers (32 rows)
+// 94, 91 and 78, 79.  The FP32 forward passes of a gradient call all stay at 8: the
+// thickness gradient is an FP64 result, and keeps its values (16 are as accurate and
+// move its seventh digit) at 0.5 % of the call.  At 128 points 16 values are slower below
+// 8192 rows (128 x 128 x 8: 3.3 + 3.2 us against 3.7 + 3.5) and a little faster above
+// (8 states: 9.5 + 8.3 against 8.7 + 8.3), so 8 for all.
+template <typename R>
+__host__ __device__ constexpr int x_vals(int M, bool gradient = false)
 {
-    return M == 256 && (sizeof(R) == 8 || !FWD) ? 16 : fft_vals(M);
+    return M == 256 && !(gradient && sizeof(R) == 4) ? 16 : fft_vals(M);
 }
 
 // Rows are numbered flat over all signals (row r = signal r / ny, y = r % ny)
@@ -144,11 +143,11 @@ __device__ __forceinline__ void real_split_inv(cpx<R>& a, cpx<R>& b, cpx<R> w, b
 // more LDS round trip) and an index division per element the two passes of
 // 64 states of 512 x 512 x 4 took 932 + 1360 us, now 630 + 565 (2.4 GB each at
 // 3.8 and 4.3 TB/s; a copy runs at 4.9), those of one 256 x 256 x 8 state 9.1 + 8.7,
-// now 6.8 + 5.4.  (With the exchange layout of FP64, pos + pos/8, in FP32 too that
+// now 6.3 + 5.4.  (With the exchange layout of FP64, pos + pos/8, in FP32 too that
 // forward pass takes 573 us and no other size gains: it waits for its stores, which
 // meet differently.)
 // ---------------------------------------------------------------------------
-template <typename R, int LX, int TYO = 0, int XV = x_vals<R, true>(LX / 2)>
+template <typename R, int LX, int TYO = 0, int XV = x_vals<R>(LX / 2)>
 __global__ __launch_bounds__((XPassShape<R, LX, TYO, XV>::NT), (XPassShape<R, LX, TYO, XV>::WPE)) void k_xfwd(
     const R* __restrict__ in, cpx<R>* __restrict__ out, int nx, int ny, int nrows, FastDiv dny,
     const cpx<R>* __restrict__ twx)
@@ -217,7 +216,7 @@ __global__ __launch_bounds__((XPassShape<R, LX, TYO, XV>::NT), (XPassShape<R, LX
 // all its pairs (k, M - k) of one row, splits them in registers and puts them
 // into LDS, where the row's group finds its first radix pass.
 // ---------------------------------------------------------------------------
-template <typename R, int LX, int TYO = 0, int XV = x_vals<R, false>(LX / 2)>
+template <typename R, int LX, int TYO = 0, int XV = x_vals<R>(LX / 2)>
 __global__ __launch_bounds__((XPassShape<R, LX, TYO, XV>::NT), (XPassShape<R, LX, TYO, XV>::WPE)) void k_xinv(
     const cpx<R>* __restrict__ in, R* __restrict__ out, int nx, int ny, int nrows, FastDiv dny,
     const cpx<R>* __restrict__ twx)

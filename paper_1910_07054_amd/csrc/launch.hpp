@@ -31,8 +31,9 @@ bool x_tile_supported(bool fp64, int LX, int ty);
 // (x-odd ones), which is the non-zero one
 hipError_t launch_xtab(int LX, const double* in, void* out, int nx, int ny, int nsig, const void* twx64,
                        hipStream_t s);
+// gradient: a forward pass of a gradient call (see x_vals)
 hipError_t launch_xfwd(bool fp64, int LX, const void* in, void* out, int nx, int ny, int nsig,
-                       const void* twx, hipStream_t s, int ty = 0);
+                       const void* twx, hipStream_t s, int ty = 0, bool gradient = false);
 hipError_t launch_xinv(bool fp64, int LX, const void* in, void* out, int nx, int ny, int nsig,
                        const void* twx, hipStream_t s, int ty = 0);
 

@@ -16,10 +16,9 @@ constexpr bool x_tile_ok()
     return S::GT * TY <= 1024 && S::GT * TY >= 64 && S::LDS <= 163840;
 }
 
-template <bool FWD, typename R, int LX, int TY>
+template <bool FWD, typename R, int LX, int TY, int XV>
 hipError_t x_one(const void* in, void* out, int nx, int ny, int nsig, const void* tw, hipStream_t s)
 {
-    constexpr int XV = x_vals<R, FWD>(LX / 2);
     if constexpr (TY == 0 || x_tile_ok<R, LX, TY, XV>()) {
         using S = XPassShape<R, LX, TY, XV>;
         const long long rows = (long long)nsig * ny;
@@ -42,17 +41,17 @@ hipError_t x_one(const void* in, void* out, int nx, int ny, int nsig, const void
     return hipErrorInvalidValue;
 }
 
-template <bool FWD, typename R, int LX>
+template <bool FWD, typename R, int LX, int XV = x_vals<R>(LX / 2)>
 hipError_t x_ty(int ty, const void* in, void* out, int nx, int ny, int nsig, const void* tw, hipStream_t s)
 {
     switch (ty) {
-    case 0: return x_one<FWD, R, LX, 0>(in, out, nx, ny, nsig, tw, s);
-    case 4: return x_one<FWD, R, LX, 4>(in, out, nx, ny, nsig, tw, s);
-    case 8: return x_one<FWD, R, LX, 8>(in, out, nx, ny, nsig, tw, s);
-    case 12: return x_one<FWD, R, LX, 12>(in, out, nx, ny, nsig, tw, s);
-    case 16: return x_one<FWD, R, LX, 16>(in, out, nx, ny, nsig, tw, s);
-    case 24: return x_one<FWD, R, LX, 24>(in, out, nx, ny, nsig, tw, s);
-    case 32: return x_one<FWD, R, LX, 32>(in, out, nx, ny, nsig, tw, s);
+    case 0: return x_one<FWD, R, LX, 0, XV>(in, out, nx, ny, nsig, tw, s);
+    case 4: return x_one<FWD, R, LX, 4, XV>(in, out, nx, ny, nsig, tw, s);
+    case 8: return x_one<FWD, R, LX, 8, XV>(in, out, nx, ny, nsig, tw, s);
+    case 12: return x_one<FWD, R, LX, 12, XV>(in, out, nx, ny, nsig, tw, s);
+    case 16: return x_one<FWD, R, LX, 16, XV>(in, out, nx, ny, nsig, tw, s);
+    case 24: return x_one<FWD, R, LX, 24, XV>(in, out, nx, ny, nsig, tw, s);
+    case 32: return x_one<FWD, R, LX, 32, XV>(in, out, nx, ny, nsig, tw, s);
     default: return hipErrorInvalidValue;
     }
 }
@@ -120,14 +119,15 @@ bool x_tile_supported(bool fp64, int LX, int ty)
     const int M = LX / 2;
     const size_t lds = (fp64 ? 16 : 8) * (size_t)ty * (size_t)(fft_region(M) | 1);
     auto ok = [&](int V) { return M / V * ty <= 1024 && M / V * ty >= 64 && lds <= 163840; };
-    // (a tile serves both directions)
-    return fp64 ? ok(x_vals<double, true>(M)) && ok(x_vals<double, false>(M))
-                : ok(x_vals<float, true>(M)) && ok(x_vals<float, false>(M));
+    // (a tile serves the passes of fields and of gradients)
+    return fp64 ? ok(x_vals<double>(M)) : ok(x_vals<float>(M)) && ok(x_vals<float>(M, true));
 }
 
 hipError_t launch_xfwd(bool fp64, int LX, const void* in, void* out, int nx, int ny, int nsig,
-                       const void* twx, hipStream_t s, int ty)
+                       const void* twx, hipStream_t s, int ty, bool gradient)
 {
+    if (!fp64 && gradient && LX == 512)
+        return x_ty<true, float, 512, x_vals<float>(256, true)>(ty, in, out, nx, ny, nsig, twx, s);
     if (fp64) return x_lx<true, double>(LX, ty, in, out, nx, ny, nsig, twx, s);
     return x_lx<true, float>(LX, ty, in, out, nx, ny, nsig, twx, s);
 }
