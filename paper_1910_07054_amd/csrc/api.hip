@@ -840,10 +840,10 @@ int path_for(hfd_plan p, int batch)
 // Rows per block of the x passes: the tuned choice, else the largest compiled
 // tile that leaves more than 192 blocks (3/4 of the CUs), at least the default
 // one of 16 (FP64 8) rows.  Taller tiles write longer runs of y per kx: the
-// forward pass of 16 states of 256 x 256 x 10 takes 149 / 116 / 106 / 94 us at
-// 8 / 16 / 24 / 32 rows.  Fewer blocks than that leave CUs idle: 128 x 128 x 8
-// (3072 rows) runs at 20.8 / 19.7 / 21.0 / 21.4 us per field, 256 x 256 x 8 (6144)
-// at 37.9 / 34.7 / 33.9 / 34.1.
+// forward pass of 16 states of 256 x 256 x 10 takes 121 / 91 / 105 / 90 us at
+// 8 / 16 / 24 / 32 rows in a field call, 149 / 116 / 106 / 94 in a gradient call.
+// Fewer blocks than that leave CUs idle: 128 x 128 x 8 (3072 rows) runs at
+// 20.8 / 19.7 / 20.9 / 21.4 us per field, 256 x 256 x 8 (6144) at 36.6 / 33.3 / 33.0 / 32.8.
 int xty_for(hfd_plan p, int batch)
 {
     auto it = p->tuned.find(batch);
